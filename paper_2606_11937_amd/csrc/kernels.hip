@@ -112,7 +112,7 @@ __device__ __forceinline__ void tc_run_trsm(double* A, int64_t lda, const TcGeom
                                             int32_t a, TcTrsmSmem& sm) {
   const int64_t r0 = tc_row0(g, I, a);
   const int64_t c0 = tc_row0(g, J, s);
-  tc_trsm_block(A + r0 * lda + c0, A + c0 * lda + c0, lda, tc_rows(g, I, a), tc_rows(g, J, s), sm);
+  tc_trsm_rows(A + r0 * lda + c0, A + c0 * lda + c0, lda, tc_rows(g, I, a), tc_rows(g, J, s), sm);
 }
 
 // Rows [64 h, 64 h + 64) of the same unit (h = 0, 1), for launches that give
@@ -169,14 +169,6 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_potrf(double* A, int64_t 
   tc_run_potrf(A, lda, g, J, s, ws.hdr, sm);
 }
 
-__global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_trsm(double* A, int64_t lda, TcGeom g, int32_t J, int32_t s,
-                                                         TcWs ws) {
-  __shared__ TcTrsmSmem sm;
-  if (tc_err_set(ws.hdr) || ws.noop) return;
-  const TcUnit u = tc_decode_trsm(g, J, s, blockIdx.x >> 1);  // two workgroups per unit
-  tc_run_trsm_half(A, lda, g, J, s, u.I, u.a, (int)(blockIdx.x & 1), sm);
-}
-
 // The panel-update and trailing-update launches each carry the next POTRF:
 // launch index 0 is the update of the next diagonal block (sub-column s+1 of
 // the panel, or sub-column 0 of the next tile column), which is its POTRF's
@@ -188,6 +180,25 @@ union alignas(512) TcUpdPotrfSmem {
   TcUpdSmem upd;
   TcPotrfSmem potrf;
 };
+
+// The TRSM launch asks for as much LDS as the panel launch that follows it.
+// Under the lookahead a pool workgroup of the bulk update may be placed above
+// a TRSM workgroup and stay for the whole bulk: the hole the TRSM leaves then
+// has to hold a panel workgroup, or that slot is lost to the panel chain
+// (with 68.6 KB against 74.2 KB, panel launches at n=32768, T=1024 averaged
+// 703 us, the longest 11.9 ms, instead of 361 us).
+union alignas(512) TcTrsmPanelSmem {
+  TcTrsmSmem trsm;
+  TcUpdPotrfSmem panel;
+};
+
+__global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_trsm(double* A, int64_t lda, TcGeom g, int32_t J, int32_t s,
+                                                         TcWs ws) {
+  __shared__ TcTrsmPanelSmem sm;
+  if (tc_err_set(ws.hdr) || ws.noop) return;
+  const TcUnit u = tc_decode_trsm(g, J, s, blockIdx.x >> 1);  // two workgroups per unit
+  tc_run_trsm_half(A, lda, g, J, s, u.I, u.a, (int)(blockIdx.x & 1), sm.trsm);
+}
 
 __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_panel(double* A, int64_t lda, TcGeom g, int32_t J, int32_t s,
                                                              TcWs ws) {

@@ -56,6 +56,11 @@ __device__ __forceinline__ tc_v4d tc_mfma(double a, double b, tc_v4d c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// c - a b: FP64 MFMAs take the sign of A as an instruction modifier
+__device__ __forceinline__ tc_v4d tc_mfma_neg(double a, double b, tc_v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
+}
+
 // Four consecutive doubles of one row, as two 16-byte loads.
 struct tc_q4 {
   tc_d2 lo, hi;
@@ -343,6 +348,86 @@ __device__ __forceinline__ void tc_wave_sync() {
 }
 
 // ---------------------------------------------------------------------------
+// Row broadcasts.  A 16-lane row of the wave holds one 16 x 16 block, lane r
+// its row r; column k of the block's factor is then lane k's register.  The
+// FP64 multiply-add takes that register straight from lane k through its
+// data-parallel operand (row_newbcast:k), one instruction where two lane
+// reads and an FMA take three: a lone wave issues one vector instruction per
+// 6 cycles here (measured: 6.0 cycles for a dependent FP64 FMA, 6.0 for this
+// broadcasting one, 26 for two lane reads and an FMA), so the instruction
+// count is what these chains cost.  Written as assembly because the compiler
+// emits a move for the broadcast; each block starts with the two wait states
+// a broadcast operand needs after a vector write (the compiler's hazard pass
+// does not look into assembly).  No operand is ever an MFMA result (those go
+// through LDS first), and the whole wave must be active.
+// ---------------------------------------------------------------------------
+#define TC_BC_ " row_newbcast:%[k"
+#define TC_BCM_ "] row_mask:0xf bank_mask:0xf\n\t"
+#define TC_FMB_(i) "v_fmac_f64_dpp %" #i ", -%[s], %[x]" TC_BC_ #i TC_BCM_
+
+// v[K0 + t] -= (src of lane K0 + t) * x for t < N, N <= 8
+template <int K0, int N>
+__device__ __forceinline__ void tc_fmac_bcast8(double (&v)[16], double src, double x) {
+  static_assert(N >= 0 && N <= 8 && K0 + N <= 16, "group of columns");
+  if constexpr (N == 8) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2) TC_FMB_(3) TC_FMB_(4) TC_FMB_(5) TC_FMB_(6) TC_FMB_(7)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2]), "+&v"(v[K0 + 3]), "+&v"(v[K0 + 4]), "+&v"(v[K0 + 5]),
+          "+&v"(v[K0 + 6]), "+&v"(v[K0 + 7])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2), [k3] "i"(K0 + 3), [k4] "i"(K0 +
+          4), [k5] "i"(K0 + 5), [k6] "i"(K0 + 6), [k7] "i"(K0 + 7));
+  } else if constexpr (N == 7) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2) TC_FMB_(3) TC_FMB_(4) TC_FMB_(5) TC_FMB_(6)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2]), "+&v"(v[K0 + 3]), "+&v"(v[K0 + 4]), "+&v"(v[K0 + 5]),
+          "+&v"(v[K0 + 6])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2), [k3] "i"(K0 + 3), [k4] "i"(K0 +
+          4), [k5] "i"(K0 + 5), [k6] "i"(K0 + 6));
+  } else if constexpr (N == 6) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2) TC_FMB_(3) TC_FMB_(4) TC_FMB_(5)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2]), "+&v"(v[K0 + 3]), "+&v"(v[K0 + 4]), "+&v"(v[K0 + 5])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2), [k3] "i"(K0 + 3), [k4] "i"(K0 +
+          4), [k5] "i"(K0 + 5));
+  } else if constexpr (N == 5) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2) TC_FMB_(3) TC_FMB_(4)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2]), "+&v"(v[K0 + 3]), "+&v"(v[K0 + 4])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2), [k3] "i"(K0 + 3), [k4] "i"(K0 +
+          4));
+  } else if constexpr (N == 4) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2) TC_FMB_(3)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2]), "+&v"(v[K0 + 3])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2), [k3] "i"(K0 + 3));
+  } else if constexpr (N == 3) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1) TC_FMB_(2)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1]), "+&v"(v[K0 + 2])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1), [k2] "i"(K0 + 2));
+  } else if constexpr (N == 2) {
+    asm("s_nop 1\n\t" TC_FMB_(0) TC_FMB_(1)
+        : "+&v"(v[K0]), "+&v"(v[K0 + 1])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0), [k1] "i"(K0 + 1));
+  } else if constexpr (N == 1) {
+    asm("s_nop 1\n\t" TC_FMB_(0)
+        : "+&v"(v[K0])
+        : [s] "v"(src), [x] "v"(x), [k0] "i"(K0));
+  }
+}
+// v[k] -= (src of lane k) * x for k = K0 .. 15
+template <int K0>
+__device__ __forceinline__ void tc_fmac_bcast(double (&v)[16], double src, double x) {
+  if constexpr (K0 < 8) {
+    tc_fmac_bcast8<K0, 8>(v, src, x);
+    tc_fmac_bcast8<K0 + 8, 8 - K0>(v, src, x);
+  } else if constexpr (K0 < 16) {
+    tc_fmac_bcast8<K0, 16 - K0>(v, src, x);
+  }
+}
+// lane K's value of v in every lane of its row
+template <int K>
+__device__ __forceinline__ double tc_bcast(double v) {
+  double o;
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1" TC_BC_ "0" TC_BCM_ : "=&v"(o) : "v"(v), [k0] "i"(K));
+  return o;
+}
+
+// ---------------------------------------------------------------------------
 // LDS images of 16 x 16 blocks.  A block row is 128 bytes: eight 16-byte
 // slots of two doubles.  Slot s of row r sits at position s ^ (r & 7) of the
 // row (the swizzle of the update kernel), so that one slot read by 16 rows,
@@ -394,23 +479,8 @@ __device__ __forceinline__ void tc_acc_put(double* blk, int lane, int rs, tc_v4d
 // k = 4 s + m of the four lane groups s, so the contraction order is fixed.
 __device__ __forceinline__ tc_v4d tc_nt16(const tc_q4& x, const tc_q4& y, tc_v4d c) {
 #pragma unroll
-  for (int m = 0; m < 4; ++m) c = tc_mfma(-tc_el(x, m), tc_el(y, m), c);
+  for (int m = 0; m < 4; ++m) c = tc_mfma_neg(tc_el(x, m), tc_el(y, m), c);
   return c;
-}
-
-// ---------------------------------------------------------------------------
-// A factored 16 x 16 diagonal block packed by columns for the substitutions:
-// column j holds 1 / L[j][j], then L[j+1 .. 15][j], padded to an even count
-// (from offset tc_ltp(j), which is even, so pairs are read 16 bytes at a
-// time; 144 doubles in all).  Columns past the block's order hold a unit
-// diagonal and zeros, so a substitution runs all 16 steps unconditionally
-// (entries past the order stay zero).
-// ---------------------------------------------------------------------------
-#define TC_LTP 144
-__host__ __device__ constexpr int tc_ltp(int j) {
-  int o = 0;
-  for (int q = 0; q < j; ++q) o += (17 - q) & ~1;
-  return o;
 }
 
 // 1 / x from the hardware estimate and two Newton-Raphson steps
@@ -421,197 +491,291 @@ __device__ __forceinline__ double tc_rcp(double x) {
   return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
 }
 
-// Forward substitution of one row against a packed diagonal block:
-//   x_j = (v_j - sum_{q<j} x_q L[j][q]) (1 / L[j][j]).
-// v holds the row on entry, x on exit.  Column-oriented: step j finishes x_j
-// and then subtracts x_j L[i][j] from every later v_i, so each v_i receives
-// the subtractions of the row-oriented form in ascending order of q; the
-// column for step j + 1 is read while step j computes.  Scaling by the
-// reciprocal of the pivot is the reference BLAS triangular solve's choice.
-__device__ __forceinline__ void tc_subst_row(double v[16], const double* lt) {
-  double cur[16];
+// ---------------------------------------------------------------------------
+// Forward substitution X <- X L^{-T} of 16 rows of X against a factored
+// 16 x 16 block L, on the matrix cores, with X in the layout of a transposed
+// MFMA result: lane l, item q holds X[l % 16][4 q + l / 16].  Item q, taken as
+// the B operand (4 x 16) of an FP64 MFMA, is X[:, 4 q .. 4 q + 3]^T, and so is
+// the first item of the MFMA's result, so the rows never change lanes.
+// Four columns (a quarter q) at a time: with N the strictly lower part of the
+// quarter's 4 x 4 diagonal block and R the reciprocals of its pivots,
+//   y <- R a,  then three times  y <- R (a - N y),
+// after which component t is r_t (a_t - sum_{k<t} l_tk x_k) for every t < 4:
+// component t takes its final value in round t, from final components only
+// (N is strictly lower), so this is the substitution itself, not an iteration
+// that converges.  Each round is one v_mfma_f64_4x4x4 (four 4 x 4 products,
+// one per four rows of X) and one multiply.  The later quarters of the block
+// then receive the product of the finished one, one such MFMA each.
+// Per 16 columns a wave issues 18 of these MFMAs (17.5 cycles each; 29 when
+// one waits for the other) and 16 multiplies.  The form it replaces, one row
+// per lane, took 120 multiply-adds of 6 cycles with three lanes in four idle
+// or repeating, and matrix and vector FP64 instructions of one wave do not
+// overlap (4 MFMAs and 32 FMAs take 473 cycles, alone 257 and 181).
+// ---------------------------------------------------------------------------
+// Lane l's operands: n[e], e = q' (q' + 1) / 2 + q, is L[4 q' + l % 4][4 q + l / 16]
+// (zero on and above the diagonal when q' == q); r[q] = 1 / L[j][j], j = 4 q + l / 16.
+struct TcMicro {
+  double n[10];
+  double r[4];
+};
+
+__device__ __forceinline__ double tc_mfma4_neg(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 1);
+}
+
+// NS independent 16-row blocks side by side.
+template <int NS>
+__device__ __forceinline__ void tc_subst16(tc_v4d (&x)[NS], const TcMicro& o) {
 #pragma unroll
-  for (int t = 0; t < 16; ++t) cur[t] = lt[t];
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * (q + 1) / 2 + q;
+    double y[NS];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    // a compiler-only barrier per step that also pins the previous result:
-    // the LDS loads of column j + 1 may overlap step j, but neither loads are
-    // hoisted nor arithmetic sunk across steps
-    if (j > 0) asm volatile("" : "+v"(v[j - 1]) : : "memory");
-    double nxt[16];
-    if (j + 1 < 16) {
+    for (int t = 0; t < NS; ++t) y[t] = x[t][q] * o.r[q];
 #pragma unroll
-      for (int t = 0; t < 15 - j; ++t) nxt[t] = lt[tc_ltp(j + 1) + t];
+    for (int it = 0; it < 3; ++it) {
+#pragma unroll
+      for (int t = 0; t < NS; ++t) y[t] = tc_mfma4_neg(o.n[e], y[t], x[t][q]);
+#pragma unroll
+      for (int t = 0; t < NS; ++t) y[t] = y[t] * o.r[q];
     }
-    v[j] = v[j] * cur[0];
 #pragma unroll
-    for (int i = j + 1; i < 16; ++i) v[i] = v[i] - v[j] * cur[i - j];
-    if (j + 1 < 16) {
+    for (int t = 0; t < NS; ++t) x[t][q] = y[t];
 #pragma unroll
-      for (int t = 0; t < 15 - j; ++t) cur[t] = nxt[t];
-    }
+    for (int p = q + 1; p < 4; ++p)
+#pragma unroll
+      for (int t = 0; t < NS; ++t) x[t][p] = tc_mfma4_neg(o.n[p * (p + 1) / 2 + q], y[t], x[t][p]);
   }
 }
 
 // ---------------------------------------------------------------------------
 // TRSM work unit: X <- X L^{-T} for mr <= 128 rows of a tile (I, J), I > J,
-// with L = L_JJ (td x td, factored).  Right-looking over 16-column blocks b:
-// forward substitution of X[:, b] against L_bb, then X[:, j] -= X[:, b] L_jb^T
-// for every block j > b (MFMA, K = 16).
-// Rows are independent, so the work is split by rows and kept in LDS, 64
-// rows at a time: wave w owns 16 of them and sweeps them alone (lanes 0..15
-// substitute one row each, all 64 lanes form the products), with no
-// workgroup barrier inside the sweep.  The diagonal blocks of L are staged
-// packed in LDS; the L_jb fragments are read from global memory one step
-// ahead (every row block of the sub-column reads them, so they stay in L2).
+// with L = L_JJ (td x td, factored).  Left-looking over 16-column blocks b:
+// X[:, b] -= X[:, c] L_bc^T for every block c < b (MFMA, K = 16), then
+// substitution against L_bb.
+// Rows are independent: a wave owns 16 of them (a strip) with its column
+// blocks in registers, in the layout above; a finished block is the B operand
+// of the products as it stands.  L passes through LDS in operand order, so
+// that each operand read is a conflict-free 16 bytes per lane: 67 KB, two
+// workgroups on a CU.
+// Step b needs only block row b of L and block b of X.  All of them are
+// loaded at the start, in that order, and block row b goes from registers to
+// LDS in front of step b, so what the later steps need arrives behind the
+// earlier ones (a CU alone takes in about 20 bytes a cycle here, 7000 cycles
+// for L and 64 rows of X; loads issued three steps ahead instead waited
+// behind the stores of the steps between, 12.7 against 11.9 us).
+// Bound by the FP64 matrix pipe of one SIMD: 112 MFMAs of 64 cycles and 8
+// substitutions (about 800 cycles each) per strip, 17000 cycles of the 28000
+// that 64 rows take alone on a CU.  In-kernel time of one workgroup: 11.9 us
+// for 64 rows (23.5 us with one row per lane in the substitution and the
+// operands of L from global memory), 20.8 us for 128 (43.6).
 // ---------------------------------------------------------------------------
-#define TC_XRS 128  // row stride of the X image, doubles
 struct alignas(16) TcTrsmSmem {
-  double x[64 * TC_XRS];  // 64 rows x 8 column blocks, swizzled within a block
-  double lt[8 * TC_LTP];  // packed diagonal blocks of L
+  double op[28][256];     // L_bc, c < b, at b (b - 1) / 2 + c: [q / 2][lane][q % 2] = L_bc[lane % 16][4 q + lane / 16]
+  double dg[8][5][16][2];  // TcMicro::n of the diagonal blocks: [b][e / 2][4 (lane / 16) + lane % 4][e % 2]
+  double rcp[128];        // reciprocals of the pivots
 };
 
-// The packed diagonal blocks of L (td x td, td <= 128); all threads take
-// part, every load issued before the first store.
-__device__ __forceinline__ void tc_trsm_stage_lt(const double* __restrict__ L, int64_t lda, int td, TcTrsmSmem& sm) {
-  const int tot = ((td + 15) >> 4) * TC_LTP;
-  double val[5];
-  bool rcp[5];
+// 4 x 4 transpose across the four 16-lane rows of the wave: lane row g,
+// register m and lane row m, register g change places.
+__device__ __forceinline__ void tc_swap_rows(double& a, double& b, bool wide) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {  // 5 * 256 >= 8 * 144
-    const int e = tc_tid() + k * TC_THREADS;
-    const int b = e / TC_LTP, q = e - b * TC_LTP;
-    int j = 0;
-#pragma unroll
-    for (int t = 1; t < 16; ++t) j += q >= tc_ltp(t);
-    const int i = j + q - tc_ltp(j);  // row of the entry (i == j: the pivot's reciprocal)
-    const int gr = 16 * b + i, gc = 16 * b + j;
-    rcp[k] = i == j;
-    val[k] = (e < tot && i < 16 && gr < td) ? L[(int64_t)gr * lda + gc] : (i == j ? 1.0 : 0.0);
+  for (int h = 0; h < 2; ++h) {
+    if (wide) {
+      const auto r = __builtin_amdgcn_permlane32_swap(x[h], y[h], false, false);
+      x[h] = r[0];
+      y[h] = r[1];
+    } else {
+      const auto r = __builtin_amdgcn_permlane16_swap(x[h], y[h], false, false);
+      x[h] = r[0];
+      y[h] = r[1];
+    }
   }
+  a = __builtin_bit_cast(double, x);
+  b = __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ tc_v4d tc_transpose4(tc_v4d v) {
+  double a = v[0], b = v[1], c = v[2], d = v[3];
+  tc_swap_rows(a, c, true);
+  tc_swap_rows(b, d, true);
+  tc_swap_rows(a, b, false);
+  tc_swap_rows(c, d, false);
+  return tc_v4d{a, b, c, d};
+}
+
+// Column block j of a strip (rows [0, mr) of X, mr <= 16) as stored: lane
+// (r, g) holds columns 16 j + 4 g .. + 3 of row r.  tc_transpose4 turns it
+// into the substitution's layout and back.  Rows past mr and columns past td
+// read clamped positions (selected to zero where they matter).
+__device__ __forceinline__ tc_v4d tc_strip_get(const double* __restrict__ X, int64_t lda, int mr, int td, int j,
+                                               int lane) {
+  const int r16 = lane & 15, c = 16 * j + 4 * (lane >> 4);
+  const int rc = r16 < mr ? r16 : (mr > 0 ? mr - 1 : 0);
+  const double* p = X + (int64_t)rc * lda;
+  if (td == 128) {
+    const tc_q4 v = tc_ld4(p + c);
+    return tc_v4d{v.lo.x, v.lo.y, v.hi.x, v.hi.y};
+  }
+  tc_v4d a;
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int e = tc_tid() + k * TC_THREADS;
-    if (e < tot) sm.lt[e] = rcp[k] ? 1.0 / val[k] : val[k];
+  for (int m = 0; m < 4; ++m) {
+    a[m] = p[c + m < td ? c + m : td - 1];
+    a[m] = c + m < td ? a[m] : 0.0;
+  }
+  return a;
+}
+__device__ __forceinline__ void tc_strip_put(double* __restrict__ X, int64_t lda, int mr, int td, int j, int lane,
+                                             tc_v4d a) {
+  const int r16 = lane & 15, c = 16 * j + 4 * (lane >> 4);
+  if (r16 >= mr) return;
+  double* g = X + (int64_t)r16 * lda + c;
+  if (td == 128) {
+    *(tc_d2*)g = tc_d2{a[0], a[1]};
+    *(tc_d2*)(g + 2) = tc_d2{a[2], a[3]};
+  } else {
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      if (c + m < td) g[m] = a[m];
   }
 }
 
-// Up to 64 rows (mr) of X against the staged diagonal blocks of L.  Starts
-// with a workgroup barrier after staging X (which also publishes the staged
-// diagonal blocks); each wave writes its own rows back at the end.
-__device__ __forceinline__ void tc_trsm_half(double* __restrict__ X, const double* __restrict__ L, int64_t lda, int mr,
-                                             int td, TcTrsmSmem& sm) {
-  const int tid = tc_tid(), lane = tid & 63, w = tid >> 6;
-  const int r16 = lane & 15, s4 = lane >> 4;
+// What a thread holds of L between its loads and their way into LDS: pass k
+// covers blocks 2 k and 2 k + 1 (waves 0-1 and 2-3; row r, columns 2 s and
+// 2 s + 1 of the block).  A full block reads whole 16-byte pairs (those of a
+// diagonal block reach above the diagonal and are dropped at the store); a
+// ragged one reads from clamped positions on or below the diagonal and
+// selects afterwards, so no load sits in a branch of its own.  Rows past td
+// are those of the identity.
+struct TcTrsmStage {
+  tc_d2 v[14], d[4];
+  double piv;
+};
+__device__ __forceinline__ tc_d2 tc_stage_pair(const double* __restrict__ L, int64_t lda, int td, int R, int C) {
+  if (td == 128) return *(const tc_d2*)(L + (int64_t)R * lda + C);
+  const int Rc = R < td ? R : td - 1, C0 = C < Rc ? C : Rc, C1 = C + 1 < Rc ? C + 1 : Rc;
+  tc_d2 v;
+  v.x = L[(int64_t)Rc * lda + C0];
+  v.y = L[(int64_t)Rc * lda + C1];
+  v.x = R < td ? v.x : 0.0;
+  v.y = R < td ? v.y : 0.0;
+  return v;
+}
+__device__ __forceinline__ void tc_stage_load(const double* __restrict__ L, int64_t lda, int td, int k,
+                                              TcTrsmStage& st) {
+  const int tid = tc_tid(), hi = tc_uniform((int32_t)(tid >> 7)), r = (tid >> 3) & 15, s = tid & 7;
+  const int p = 2 * k + hi;
+  int bi = 1;
+#pragma unroll
+  for (int q = 2; q < 8; ++q) bi += p >= q * (q - 1) / 2;
+  const int bj = p - bi * (bi - 1) / 2;
+  st.v[k] = tc_stage_pair(L, lda, td, 16 * bi + r, 16 * bj + 2 * s);
+}
+__device__ __forceinline__ void tc_stage_put(TcTrsmSmem& sm, int k, const TcTrsmStage& st) {
+  const int tid = tc_tid(), hi = tc_uniform((int32_t)(tid >> 7)), r = (tid >> 3) & 15, s = tid & 7;
+  // columns c = 2 s and c + 1 lie in quarter s / 2 at c % 4 and c % 4 + 1
+  double* g = sm.op[2 * k + hi] + (s >> 2) * 128 + (((2 * s) & 3) * 16 + r) * 2 + ((s >> 1) & 1);
+  g[0] = st.v[k].x;
+  g[32] = st.v[k].y;
+}
+__device__ __forceinline__ void tc_stage_diag(const double* __restrict__ L, int64_t lda, int td, TcTrsmStage& st) {
+  const int tid = tc_tid(), hi = tc_uniform((int32_t)(tid >> 7)), r = (tid >> 3) & 15, s = tid & 7;
+  const int i = tid & 127;
+  st.piv = L[(int64_t)(i < td ? i : td - 1) * (lda + 1)];
+  st.piv = i < td ? st.piv : 1.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c0 = 16 * (2 * k + hi);
+    st.d[k] = tc_stage_pair(L, lda, td, c0 + r, c0 + 2 * s);
+  }
+}
+__device__ __forceinline__ void tc_stage_diag_put(TcTrsmSmem& sm, const TcTrsmStage& st) {
+  const int tid = tc_tid(), hi = tc_uniform((int32_t)(tid >> 7)), r = (tid >> 3) & 15, s = tid & 7;
+  const int qr = r >> 2, qc = s >> 1, k4 = (2 * s) & 3;
+  const int e = qr * (qr + 1) / 2 + qc;
+  double* g = &sm.dg[0][0][0][0] + ((e >> 1) * 16 + 4 * k4 + (r & 3)) * 2 + (e & 1);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (qc <= qr) {
+      g[(2 * k + hi) * 160] = 2 * s < r ? st.d[k].x : 0.0;
+      g[(2 * k + hi) * 160 + 8] = 2 * s + 1 < r ? st.d[k].y : 0.0;
+    }
+  }
+  if (tid < 128) sm.rcp[tid] = 1.0 / st.piv;
+}
+// passes that hold block row b's last block
+__host__ __device__ constexpr int tc_stage_end(int b) { return (b * (b + 1) / 2 + 1) / 2; }
+
+// Step B of a strip.  FIRST: the workgroup's first strips, whose steps also
+// move block row B of L into LDS (all waves, one barrier).
+template <int B, bool FIRST>
+__device__ __forceinline__ void tc_trsm_step(double* __restrict__ X, int64_t lda, int mr, int td, int nbk, int lane,
+                                             tc_v4d (&x)[8], const TcTrsmStage& st, TcTrsmSmem& sm) {
+  const int s4 = lane >> 4;
+  if constexpr (FIRST) {
+    if constexpr (B == 0) tc_stage_diag_put(sm, st);
+    if constexpr (B > 0) {
+#pragma unroll
+      for (int k = tc_stage_end(B - 1); k < tc_stage_end(B); ++k) tc_stage_put(sm, k, st);
+    }
+    __syncthreads();
+  }
+  TcMicro o;
+#pragma unroll
+  for (int t = 0; t < 5; ++t) {
+    const tc_d2a16 p = *(const tc_d2a16*)&sm.dg[B][t][4 * s4 + (lane & 3)][0];
+    o.n[2 * t] = p.x;
+    o.n[2 * t + 1] = p.y;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o.r[q] = sm.rcp[16 * B + 4 * q + s4];
+  tc_v4d y[1] = {tc_transpose4(x[B])};
+#pragma unroll
+  for (int c = 0; c < B; ++c) {
+    const double* f = sm.op[B * (B - 1) / 2 + c] + 2 * lane;
+    const tc_d2a16 lo = *(const tc_d2a16*)f, hi = *(const tc_d2a16*)(f + 128);
+    y[0] = tc_mfma_neg(lo.x, x[c][0], y[0]);
+    y[0] = tc_mfma_neg(lo.y, x[c][1], y[0]);
+    y[0] = tc_mfma_neg(hi.x, x[c][2], y[0]);
+    y[0] = tc_mfma_neg(hi.y, x[c][3], y[0]);
+  }
+  tc_subst16(y, o);
+  x[B] = y[0];
+  tc_strip_put(X, lda, mr, td, B, lane, tc_transpose4(y[0]));
+  if constexpr (B + 1 < 8) {
+    if (B + 1 < nbk) tc_trsm_step<B + 1, FIRST>(X, lda, mr, td, nbk, lane, x, st, sm);
+  }
+}
+
+// A TRSM unit, or the mr <= 64 rows of half a unit as a workgroup of its own
+// (each row's arithmetic is the same): wave w takes the strips w and w + 4.
+__device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const double* __restrict__ L, int64_t lda,
+                                             int mr_in, int td_in, TcTrsmSmem& sm) {
+  const int mr = tc_uniform((int32_t)mr_in), td = tc_uniform((int32_t)td_in);
+  const int tid = tc_tid(), lane = tid & 63;
+  const int w = tc_uniform((int32_t)(tid >> 6));
   const int nbk = (td + 15) >> 4;
-  {  // X rows [0, mr) x columns [0, td), zero elsewhere: 16 slots per thread
-    tc_d2 v[16];
+  // rows of the strip at r0; a wave without one runs along on row 0 and stores nothing
+  auto rows = [&](int r0) { return mr - r0 < 16 ? (mr > r0 ? mr - r0 : 0) : 16; };
+  double* X0 = X + (16 * w < mr ? (int64_t)(16 * w) * lda : 0);
+  tc_v4d x[8];
+  TcTrsmStage st;
+  tc_stage_diag(L, lda, td, st);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int row = 4 * k + w, c = 2 * lane;
-      const double* p = X + (int64_t)row * lda + c;
-      v[k].x = (row < mr && c < td) ? p[0] : 0.0;
-      v[k].y = (row < mr && c + 1 < td) ? p[1] : 0.0;
-    }
+  for (int b = 0; b < 8; ++b) {
+    x[b] = tc_strip_get(X0, lda, rows(16 * w), td, b, lane);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int row = 4 * k + w;
-      tc_d2a16 p;
-      p.x = v[k].x;
-      p.y = v[k].y;
-      *(tc_d2a16*)(sm.x + row * TC_XRS + (lane >> 3) * 16 + (((lane & 7) ^ (row & 7)) << 1)) = p;
-    }
+    for (int k = b > 0 ? tc_stage_end(b - 1) : 0; k < tc_stage_end(b); ++k) tc_stage_load(L, lda, td, k, st);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  // fragments of L_jb (lane (r16, s4): row 16 j + r16, columns 16 b + 4 s4 ..)
-  tc_q4 fa[7], fb[7];
-  auto load_frags = [&](tc_q4 f[7], int b) {
+  tc_trsm_step<0, true>(X0, lda, rows(16 * w), td, nbk, lane, x, st, sm);
+  if (16 * w + 64 < mr) {
+    asm volatile("" ::: "memory");  // operands are read from LDS again, not kept in registers
+    double* X1 = X0 + 64 * lda;
 #pragma unroll
-    for (int jj = 0; jj < 7; ++jj) {
-      const int row = 16 * (b + 1 + jj) + r16;
-      if (b + 1 + jj < nbk) {
-        if (row < td) {
-          f[jj] = tc_ld4(L + (int64_t)row * lda + 16 * b + 4 * s4);
-        } else {
-          f[jj].lo = tc_d2{0.0, 0.0};
-          f[jj].hi = tc_d2{0.0, 0.0};
-        }
-      }
-    }
-  };
-  if (nbk > 1) load_frags(fa, 0);
-  __syncthreads();
-
-  double* xw = sm.x + 16 * w * TC_XRS;  // this wave's 16 rows
-  // step b with its fragments in cur; the next step's are loaded into nxt
-  // between the substitution and the products, so they land behind this
-  // step's products and the next substitution
-  auto step = [&](int b, tc_q4 (&cur)[7], tc_q4 (&nxt)[7]) {
-    if (lane < 16) {
-      double v[16];
-      tc_row_get(xw + 16 * b, lane, TC_XRS, v);
-      tc_subst_row(v, sm.lt + b * TC_LTP);
-      tc_row_put(xw + 16 * b, lane, TC_XRS, v);
-    }
-    tc_wave_sync();
-    if (b + 1 < nbk) {
-      if (b + 2 < nbk) load_frags(nxt, b + 1);
-      const tc_q4 xb = tc_frag_get(xw + 16 * b, r16, s4, TC_XRS);
-      // blocks j = b + 1 + jj in two groups (4 + 3), each group's MFMA
-      // chains interleaved
-#pragma unroll
-      for (int g0 = 0; g0 < 7; g0 += 4) {
-        tc_v4d acc[4];
-#pragma unroll
-        for (int jj = g0; jj < g0 + 4 && jj < 7; ++jj)
-          if (b + 1 + jj < nbk) acc[jj - g0] = tc_acc_get(xw + 16 * (b + 1 + jj), lane, TC_XRS);
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-          for (int jj = g0; jj < g0 + 4 && jj < 7; ++jj)
-            if (b + 1 + jj < nbk) acc[jj - g0] = tc_mfma(-tc_el(xb, m), tc_el(cur[jj], m), acc[jj - g0]);
-#pragma unroll
-        for (int jj = g0; jj < g0 + 4 && jj < 7; ++jj)
-          if (b + 1 + jj < nbk) tc_acc_put(xw + 16 * (b + 1 + jj), lane, TC_XRS, acc[jj - g0]);
-      }
-      tc_wave_sync();
-    }
-  };
-  for (int b = 0; b < nbk; b += 2) {
-    step(b, fa, fb);
-    if (b + 1 < nbk) step(b + 1, fb, fa);
-  }
-  // this wave's rows back to X
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int row = 16 * w + k, c = 2 * lane;
-    if (row < mr) {
-      const tc_d2a16 p = *(const tc_d2a16*)(sm.x + row * TC_XRS + (lane >> 3) * 16 + (((lane & 7) ^ (row & 7)) << 1));
-      double* g = X + (int64_t)row * lda + c;
-      if (c < td) g[0] = p.x;
-      if (c + 1 < td) g[1] = p.y;
-    }
-  }
-}
-
-// One half (mr <= 64 rows) of a TRSM unit, as a workgroup of its own.
-__device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const double* __restrict__ L, int64_t lda, int mr,
-                                             int td, TcTrsmSmem& sm) {
-  mr = tc_uniform((int32_t)mr);
-  td = tc_uniform((int32_t)td);
-  tc_trsm_stage_lt(L, lda, td, sm);
-  tc_trsm_half(X, L, lda, mr, td, sm);
-}
-
-// A whole TRSM unit (mr <= 128 rows): its halves one after the other.  Each
-// row's arithmetic is the same as in tc_trsm_rows.
-__device__ __forceinline__ void tc_trsm_block(double* __restrict__ X, const double* __restrict__ L, int64_t lda, int mr,
-                                              int td, TcTrsmSmem& sm) {
-  mr = tc_uniform((int32_t)mr);
-  td = tc_uniform((int32_t)td);
-  tc_trsm_stage_lt(L, lda, td, sm);
-  for (int h = 0; h < mr; h += 64) {
-    if (h > 0) __syncthreads();  // the previous half's write-back has read the X image
-    tc_trsm_half(X + (int64_t)h * lda, L, lda, mr - h < 64 ? mr - h : 64, td, sm);
+    for (int b = 0; b < 8; ++b) x[b] = tc_strip_get(X1, lda, rows(16 * w + 64), td, b, lane);
+    tc_trsm_step<0, false>(X1, lda, rows(16 * w + 64), td, nbk, lane, x, st, sm);
   }
 }
 
@@ -624,26 +788,36 @@ __device__ __forceinline__ void tc_trsm_block(double* __restrict__ X, const doub
 //      (lane i holds row i; right-looking over the block's columns, the
 //      POTRF definition on the block; the pivot and the column entries each
 //      step needs are read from their owner lanes);
-//   2. blocks (i, b), i > b: forward substitution against L_bb, one row per
-//      thread;
+//   2. blocks (i, b), i > b: forward substitution against L_bb (tc_subst16):
+//      wave 0 takes block b + 1, waves 1 .. 3 two of the others each;
 //   3. blocks (i, j), b < j <= i: A_ij -= L_ib L_jb^T (MFMA, K = 16).
-// In step 3 wave 0 updates only block (b+1, b+1) and then factors it (step 1
-// of b+1) while waves 1..3 update the other blocks.
+// In step 3 wave 0 updates only block (b+1, b+1), straight from the registers
+// of its own substitution, and then factors it (step 1 of b+1) while waves
+// 1..3 update the other blocks.
+// In-kernel time of one workgroup with a 128 x 128 tile: 24.0 us (43.0 us
+// with two lane reads per broadcast, the library square root, a substitution
+// with one row per thread and predicated loads).  What bounds it: the 16
+// pivots of a diagonal block are one wave's chain of about 210 cycles each,
+// 27000 of the 57000 cycles; the copy in and out takes 12000.
 // A pivot d <= 0 or NaN stops the factorization: returns the 0-based in-tile
 // column, else -1 (the tile is then left partly factored).
 // ---------------------------------------------------------------------------
 struct alignas(16) TcPotrfSmem {
   double blk[36][256];  // packed lower triangle
-  double lt[TC_LTP];    // the current diagonal block, packed by columns
+  double rcp[16];       // reciprocals of the current diagonal block's pivots
   int fail;
 };
 
 __device__ __forceinline__ int tc_pk(int i, int j) { return i * (i + 1) / 2 + j; }
 
-// Lower triangle of D (rows and columns < td) into the packed blocks (zeros
-// elsewhere), or (OUT) back into D.  Pass k moves blocks 2 k and 2 k + 1
-// (waves 0-1 and 2-3, 16 rows x 8 slots each), so the block of a pass is
-// uniform per wave; all loads are issued before the first store.
+// Lower triangle of D (rows and columns < td) into the packed blocks, or
+// (OUT) back into D.  Pass k moves blocks 2 k and 2 k + 1 (waves 0-1 and 2-3,
+// 16 rows x 8 slots each), so the block of a pass is uniform per wave; all
+// loads are issued before the first store.  A full tile moves 16-byte pairs:
+// those of a diagonal block reach above the diagonal on the way in (entries
+// that never feed one on or below it) and are masked on the way out.  A
+// ragged tile reads from clamped positions on or below the diagonal and
+// selects afterwards (zero past td), so no load waits in a branch of its own.
 template <bool OUT>
 __device__ __forceinline__ void tc_pk_copy(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm) {
   const int tid = tc_tid();
@@ -652,82 +826,131 @@ __device__ __forceinline__ void tc_pk_copy(double* __restrict__ D, int64_t lda, 
   const int hi = tc_uniform((int32_t)(tid >> 7));
   const int r = (tid >> 3) & 15, s = tid & 7;
   double* const lrow = &sm.blk[0][0] + r * 16 + ((s ^ (r & 7)) << 1);
-  tc_d2 v[18];
+  auto pos = [&](int p, int& bi, int& bj) {
+    bi = 0;
 #pragma unroll
-  for (int k = 0; k < 18; ++k) {
-    const int p = 2 * k + hi;
-    if (p < nblk) {
-      int bi = 0;
-#pragma unroll
-      for (int q = 1; q < 8; ++q) bi += p >= q * (q + 1) / 2;
-      const int bj = p - bi * (bi + 1) / 2;
-      const int R = 16 * bi + r, C = 16 * bj + 2 * s;
-      double* g = D + (int64_t)R * lda + C;
-      if (OUT) {
-        if (R < td) {
-          const tc_d2a16 x = *(const tc_d2a16*)(lrow + p * 256);
-          if (C <= R) g[0] = x.x;
-          if (C + 1 <= R) g[1] = x.y;
-        }
-      } else {
-        v[k].x = (R < td && C <= R) ? g[0] : 0.0;
-        v[k].y = (R < td && C + 1 <= R) ? g[1] : 0.0;
-      }
-    }
-  }
-  if (!OUT) {
+    for (int q = 1; q < 8; ++q) bi += p >= q * (q + 1) / 2;
+    bj = p - bi * (bi + 1) / 2;
+  };
+  if constexpr (OUT) {
 #pragma unroll
     for (int k = 0; k < 18; ++k) {
       const int p = 2 * k + hi;
-      if (p < nblk) {
-        tc_d2a16 x;
-        x.x = v[k].x;
-        x.y = v[k].y;
-        *(tc_d2a16*)(lrow + p * 256) = x;
+      if (p >= nblk) break;
+      int bi, bj;
+      pos(p, bi, bj);
+      const int R = 16 * bi + r, C = 16 * bj + 2 * s;
+      double* g = D + (int64_t)R * lda + C;
+      const tc_d2a16 x = *(const tc_d2a16*)(lrow + p * 256);
+      if (td == 128 && bi != bj) {
+        *(tc_d2*)g = tc_d2{x.x, x.y};
+      } else if (R < td) {
+        if (C <= R) g[0] = x.x;
+        if (C + 1 <= R) g[1] = x.y;
       }
+    }
+  } else {
+    tc_d2 v[18];
+#pragma unroll
+    for (int k = 0; k < 18; ++k) {
+      int bi, bj;
+      pos(2 * k + hi, bi, bj);
+      const int R = 16 * bi + r, C = 16 * bj + 2 * s;
+      if (td == 128) {
+        v[k] = *(const tc_d2*)(D + (int64_t)R * lda + C);
+      } else {
+        const int Rc = R < td ? R : td - 1, C0 = C < Rc ? C : Rc, C1 = C + 1 < Rc ? C + 1 : Rc;
+        v[k].x = D[(int64_t)Rc * lda + C0];
+        v[k].y = D[(int64_t)Rc * lda + C1];
+        v[k].x = R < td && C <= R ? v[k].x : 0.0;
+        v[k].y = R < td && C + 1 <= R ? v[k].y : 0.0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 18; ++k) {
+      tc_d2a16 x;
+      x.x = v[k].x;
+      x.y = v[k].y;
+      *(tc_d2a16*)(lrow + (2 * k + hi) * 256) = x;
     }
   }
 }
 
+// Pivot J of the diagonal block held one row per lane (the same in every
+// 16-lane row of the wave), and the trailing update a_ik -= l_ij l_kj.  The
+// square root and its reciprocal come from one hardware estimate of
+// 1 / sqrt(d) (5e-8): a third-order step for the reciprocal root, then one
+// residual correction each for the root and for 1 / root.  In the range the
+// caller checks, root and reciprocal are the bits of sqrt(d) and 1 / sqrt(d)
+// (4M random values in [1, 4) and all squares up to 60000^2; 426 roots
+// differed in 4M over the whole exponent range, below 2^-767), in 70 cycles
+// of one wave against about 150 for the two library sequences.  m collects
+// the smallest high word of a pivot; a pivot of zero, infinity or NaN turns
+// every later one of the block into NaN.
+#define TC_PIV_LO ((1023 - 700) << 20)  // 2^-700
+template <int J>
+__device__ __forceinline__ void tc_diag_steps(double (&a)[16], double (&s)[16], double (&r)[16], int32_t& m) {
+  const double d = tc_bcast<J>(a[J]);
+  const int32_t dh = (int32_t)(__builtin_bit_cast(uint64_t, d) >> 32);
+  m = dh < m ? dh : m;
+  const double y0 = __builtin_amdgcn_rsq(d);
+  const double e = __builtin_fma(-(d * y0), y0, 1.0);
+  const double y = __builtin_fma(y0 * e, __builtin_fma(e, 0.375, 0.5), y0);
+  const double s0 = d * y;
+  s[J] = __builtin_fma(__builtin_fma(-s0, s0, d), 0.5 * y, s0);
+  r[J] = __builtin_fma(y, __builtin_fma(-s[J], y, 1.0), y);
+  a[J] = a[J] * r[J];
+  tc_fmac_bcast<J + 1>(a, a[J], a[J]);
+  if constexpr (J + 1 < 16) tc_diag_steps<J + 1>(a, s, r, m);
+}
+
 // Step 1 on diagonal block b (nb valid columns, column offset c0 in the
-// tile) by the calling wave: factors the block in place, stages it packed in
-// lt, and records the first failing pivot in fail.  Lane i < 16 holds row i.
-// The 16 steps are free of branches, so the compiler can overlap a step's
-// trailing update with the next pivot: entries above the diagonal are
-// updated too (they never feed an entry on or below it and are never
-// stored), columns past nb take a unit pivot, and after a failing pivot the
-// values are unspecified.
+// tile) by the calling wave: factors the block in place, leaves the
+// reciprocals of its pivots in rcp, and records the first failing pivot in
+// fail.  Columns past nb take a unit pivot.  Entries above the diagonal are
+// updated too; they never feed an entry on or below it.
+// A pivot below 2^-700 (so any that is not positive) or not finite sends the
+// block through the plain form below, from its untouched image in LDS.
 __device__ __forceinline__ void tc_pk_diag(TcPotrfSmem& sm, int b, int nb, int c0) {
-  const int lane = tc_tid() & 63;
+  const int lane = tc_tid() & 63, r16 = lane & 15;
   double* blk = sm.blk[tc_pk(b, b)];
-  double a[16];
-  tc_row_get(blk, lane & 15, 16, a);
-  // the 16 steps form one branch-free block (selects only; lane j keeps its
-  // pivot's reciprocal and stores it after the loop), so the scheduler can
-  // run a step's remaining updates under the next pivot's square root
+  double a[16], s[16], r[16];
+  tc_row_get(blk, r16, 16, a);
+  if (nb < 16) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = (r16 == k && k >= nb) ? 1.0 : a[k];
+  }
+  int32_t m = INT32_MAX;
+  tc_diag_steps<0>(a, s, r, m);
+  if (__builtin_expect(tc_uniform((int32_t)(m >= TC_PIV_LO && s[15] == s[15])) != 0, 1)) {
+    if (lane < nb) tc_row_put(blk, lane, 16, a);
+    tc_wave_sync();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      blk[tc_bo(j, j, 16)] = s[j];
+      sm.rcp[j] = r[j];
+    }
+    return;
+  }
   int bad = -1;
-  double myr = 1.0;
-#pragma unroll
+#pragma unroll 1
   for (int j = 0; j < 16; ++j) {
-    const bool live = j < nb;
-    const double d = tc_readlane(a[j], j);
-    bad = (bad < 0 && live && !(d > 0.0)) ? j : bad;
-    const double ljj = sqrt(live ? d : 1.0);
-    const double rj = tc_rcp(ljj);
-    a[j] = lane == j ? ljj : a[j] * rj;
-    myr = lane == j ? rj : myr;
-    // trailing update a_ik -= l_ij l_kj for k > j
-#pragma unroll
-    for (int k = j + 1; k < 16; ++k) a[k] = __builtin_fma(-a[j], tc_readlane(a[j], k), a[k]);
+    const double d = j < nb ? blk[tc_bo(j, j, 16)] : 1.0;
+    if (bad < 0 && !(d > 0.0)) bad = j;
+    const double ljj = sqrt(d), rj = tc_rcp(ljj);
+    if (lane == 0) sm.rcp[j] = rj;
+    if (j >= nb) continue;
+    const double l = blk[tc_bo(r16, j, 16)] * rj;
+    tc_wave_sync();
+    if (lane < 16 && lane >= j) blk[tc_bo(lane, j, 16)] = lane == j ? ljj : l;
+    tc_wave_sync();
+#pragma unroll 1
+    for (int k = j + 1; k < nb; ++k)
+      if (lane < 16 && lane >= k)
+        blk[tc_bo(lane, k, 16)] = __builtin_fma(-l, blk[tc_bo(k, j, 16)], blk[tc_bo(lane, k, 16)]);
+    tc_wave_sync();
   }
   if (lane == 0 && bad >= 0) sm.fail = c0 + bad;
-  if (lane < 16) {
-    sm.lt[tc_ltp(lane)] = myr;
-#pragma unroll
-    for (int k = 0; k < 15; ++k)
-      if (k < lane) sm.lt[tc_ltp(k) + (lane - k)] = lane < nb ? a[k] : 0.0;
-  }
-  if (lane < nb) tc_row_put(blk, lane, 16, a);
 }
 
 __device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda, int td_in, TcPotrfSmem& sm) {
@@ -743,54 +966,79 @@ __device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda
   __syncthreads();
   int fail = tc_uniform((int32_t)sm.fail);
   for (int b = 0; fail < 0 && b + 1 < nbk; ++b) {
-    // 2. the blocks below diagonal block b, one row per thread
-    if (tid < td - 16 * (b + 1)) {
-      double* blk = sm.blk[tc_pk(b + 1 + (tid >> 4), b)];
-      double v[16];
-      tc_row_get(blk, tid & 15, 16, v);
-      tc_subst_row(v, sm.lt);
-      tc_row_put(blk, tid & 15, 16, v);
+    // 2. the blocks below diagonal block b
+    tc_v4d x[2];
+    {
+      TcMicro o;
+      const double* db = sm.blk[tc_pk(b, b)];
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q <= p; ++q) {
+          const double v = db[tc_bo(4 * p + (lane & 3), 4 * q + s4, 16)];
+          o.n[p * (p + 1) / 2 + q] = (p > q || (lane & 3) > s4) ? v : 0.0;
+        }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o.r[q] = sm.rcp[4 * q + s4];
+      // wave 0: block b + 1; wave w: blocks b + 2 w and b + 2 w + 1
+      const int i0 = wu == 0 ? b + 1 : b + 2 * wu, i1 = i0 + 1;
+      double* x0 = sm.blk[tc_pk(i0 < nbk ? i0 : b, b)];
+      double* x1 = sm.blk[tc_pk(i1 < nbk ? i1 : b, b)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        x[0][q] = x0[tc_bo(r16, 4 * q + s4, 16)];
+        x[1][q] = x1[tc_bo(r16, 4 * q + s4, 16)];
+      }
+      if (wu != 0 && i1 < nbk) {
+        tc_subst16(x, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          x0[tc_bo(r16, 4 * q + s4, 16)] = x[0][q];
+          x1[tc_bo(r16, 4 * q + s4, 16)] = x[1][q];
+        }
+      } else if (i0 < nbk) {
+        tc_v4d y[1] = {x[0]};
+        tc_subst16(y, o);
+        x[0] = y[0];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x0[tc_bo(r16, 4 * q + s4, 16)] = x[0][q];
+      }
     }
     __syncthreads();
     // 3. the trailing blocks, numbered u = ii (ii + 1) / 2 + jj for block
     //    (b + 1 + ii, b + 1 + jj), jj <= ii; u = 0 is the next diagonal block
     if (wu == 0) {
       double* cb = sm.blk[tc_pk(b + 1, b + 1)];
-      const tc_q4 x = tc_frag_get(sm.blk[tc_pk(b + 1, b)], r16, s4, 16);
-      tc_acc_put(cb, lane, 16, tc_nt16(x, x, tc_acc_get(cb, lane, 16)));
+      tc_v4d c = tc_acc_get(cb, lane, 16);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c = tc_mfma_neg(x[0][q], x[0][q], c);
+      tc_acc_put(cb, lane, 16, c);
       tc_wave_sync();
       const int c1 = 16 * (b + 1);
       tc_pk_diag(sm, b + 1, td - c1 < 16 ? td - c1 : 16, c1);
     } else {
-      // wave w takes u = w, w + 3, ..., four blocks at a time with their
-      // MFMA chains interleaved
-      const int m = nbk - 1 - b, cnt = m * (m + 1) / 2;
-      for (int u0 = wu; u0 < cnt; u0 += 12) {
-        int off[4];
-        tc_q4 x[4], y[4];
-        tc_v4d acc[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int u = u0 + 3 * q;
-          int ii = 0;
-#pragma unroll
-          for (int t = 1; t < 7; ++t) ii += u >= t * (t + 1) / 2;
-          const int i = b + 1 + ii, j = b + 1 + u - ii * (ii + 1) / 2;
-          off[q] = tc_pk(i, j) * 256;
-          if (u < cnt) {
-            x[q] = tc_frag_get(sm.blk[tc_pk(i, b)], r16, s4, 16);
-            y[q] = tc_frag_get(sm.blk[tc_pk(j, b)], r16, s4, 16);
-            acc[q] = tc_acc_get(&sm.blk[0][0] + off[q], lane, 16);
+      // block rows b + ii, ii = 2 .. m: ii blocks each.  Wave w takes rows
+      // m + 1 - w and m - 6 + w (where they are at least 2), which splits the
+      // 27 blocks of b = 0 into nine each and the rest within one or two.
+      const int m = nbk - 1 - b;
+#pragma unroll 1
+      for (int h = 0; h < 2; ++h) {
+        const int ii = h == 0 ? m + 1 - wu : m - 6 + wu;
+        if (ii < 2) continue;
+        const tc_q4 xi = tc_frag_get(sm.blk[tc_pk(b + ii, b)], r16, s4, 16);
+        double* cb = sm.blk[tc_pk(b + ii, b + 1)];  // the row's blocks are consecutive
+        tc_q4 y = tc_frag_get(sm.blk[tc_pk(b + 1, b)], r16, s4, 16);
+        tc_v4d c = tc_acc_get(cb, lane, 16);
+#pragma unroll 1
+        for (int j = 1; j <= ii; ++j) {
+          const tc_q4 yj = y;
+          const tc_v4d cj = c;
+          if (j < ii) {  // the next block's operands, behind this one's products
+            y = tc_frag_get(sm.blk[tc_pk(b + j + 1, b)], r16, s4, 16);
+            c = tc_acc_get(cb + j * 256, lane, 16);
           }
+          tc_acc_put(cb + (j - 1) * 256, lane, 16, tc_nt16(xi, yj, cj));
         }
-#pragma unroll
-        for (int mm = 0; mm < 4; ++mm)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (u0 + 3 * q < cnt) acc[q] = tc_mfma(-tc_el(x[q], mm), tc_el(y[q], mm), acc[q]);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (u0 + 3 * q < cnt) tc_acc_put(&sm.blk[0][0] + off[q], lane, 16, acc[q]);
       }
     }
     __syncthreads();

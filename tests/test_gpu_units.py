@@ -1,0 +1,79 @@
+"""Edges of the POTRF and TRSM bodies, through chol_factor.
+
+A pivot below 2^-700 or not finite takes the plain form of the 16 x 16
+diagonal factorization, every other one the fast form; ragged tiles take the
+clamped loads and masked stores.  Tolerances, fixed in advance:
+  scaling   A 4^k has the factor 2^k L.  Nothing underflows at the scales
+            used, so the two factors are factorizations of the same matrix by
+            the same operations up to one rounding of a pivot's reciprocal;
+            they agree within the row-scaled error of a stable factorization,
+            n u kappa <= 200 * 2^-53 * 5 < 1.2e-13.
+  shapes    e_row <= 1e-10 against the oracle, the bar of the parity tests.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_11937_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tc():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_11937_amd import tilechol
+    return tilechol
+
+
+def factor(tc, A, T, sched="fork_join"):
+    import torch
+    L = torch.from_numpy(A.copy()).cuda()
+    info = tc.chol_factor(L, T, sched)
+    return L.cpu().numpy(), info
+
+
+@pytest.mark.parametrize("n,T", [(1, 128), (5, 128), (16, 128), (33, 128), (130, 128), (200, 64)])
+@pytest.mark.parametrize("half", [-390, -351, 480])
+def test_pivot_range(tc, n, T, half):
+    """Pivots near 2^-780 and 2^-702 (plain form) and 2^960 (fast form)."""
+    A = inputs.gg_plus_identity(n, seed=n)
+    L, info = factor(tc, A, T)
+    S, info_s = factor(tc, A * 2.0 ** (2 * half), T)
+    assert info == info_s == 0
+    d = np.abs(np.tril(S) * 2.0 ** -half - np.tril(L)) / np.sqrt(np.diag(A))[:, None]
+    print(f"n={n} T={T} 2^{2 * half}: row-scaled difference {d.max():.2e}")
+    assert d.max() <= 1.2e-13
+
+
+@pytest.mark.parametrize("k", [0, 1, 15, 16, 31, 100, 127, 128, 129])
+@pytest.mark.parametrize("value", [-1.0, 0.0, float("nan")])
+def test_failing_pivot_position(tc, k, value):
+    """The first failing pivot is reported wherever it lies in a 16-column
+    block, with earlier blocks factored by the fast form."""
+    A = np.eye(130) * 4.0
+    A[k, k] = value
+    for j in range(k + 1, 130):
+        A[j, j] = -2.0  # later failures do not count
+    for sched in ("fork_join", "async_dag"):
+        _, info = factor(tc, A, 128, sched)
+        assert info == k + 1
+
+
+@pytest.mark.parametrize("T,n", [(1, 5), (3, 10), (15, 40), (16, 33), (17, 60), (100, 260), (127, 300), (128, 129),
+                                 (128, 143), (128, 192), (128, 193), (129, 300)])
+def test_ragged_tiles(tc, T, n):
+    A = inputs.gg_plus_identity(n, seed=T)
+    ref, info = oracle.potrf(A)
+    assert info == 0
+    for sched in ("fork_join", "async_dag"):
+        L, got = factor(tc, A, T, sched)
+        assert got == 0
+        e = oracle.row_scaled_error(L, ref, A)
+        print(f"T={T} n={n} {sched}: e_row {e:.2e}")
+        assert e <= 1e-10
+        assert np.array_equal(np.triu(L, 1), np.triu(A, 1))
