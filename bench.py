@@ -158,17 +158,24 @@ def make_input(n: int):
     return inputs.se_kernel_device(n, seed=1, device="cuda")
 
 
-def update_flops(n: int, T: int, beyond_next: bool = False) -> float:
+def update_flops(n: int, T: int, beyond_next: bool = False, one_launch_units: int = 0) -> float:
     """Algorithmic flops of all SYRK + GEMM tile operations (T^3 per SYRK,
     2 T^3 per GEMM, on the tiles' actual sides when T does not divide n).
     beyond_next: only the output tiles (I, K) with K > J + 1 of each step J,
-    the part the lookahead schedule runs on its second stream."""
+    the part the lookahead schedule runs on its second stream; steps of at
+    most one_launch_units 128 x 128 units, which it does not split, are left
+    out."""
     M = -(-n // T)
     side = [min(T, n - I * T) for I in range(M)]
     f = 0.0
     for J in range(M):
         t = side[J]
         k0 = J + 2 if beyond_next else J + 1
+        if beyond_next:
+            blocks = [-(-side[I] // 128) for I in range(J + 1, M)]
+            below = sum(blocks)
+            if sum(b * (b + 1) // 2 for b in blocks) + (below * below - sum(b * b for b in blocks)) // 2 <= one_launch_units:
+                continue
         for I in range(k0, M):
             f += side[I] * side[I] * t  # SYRK(I, J)
             for K in range(k0, I):
@@ -697,7 +704,11 @@ def main():
     tc.chol_timing_read(st)  # discard anything recorded before
     # time the dominant kernel's launches only: every event pair costs a few
     # microseconds on the stream
-    tc.chol_timing_enable(["update_rest"] if sched == "fork_join_lookahead" else
+    # (the lookahead schedule splits a step's update over two streams only when
+    # its units exceed the chip, and never with tiles of one 128-wide block)
+    rest_flops = update_flops(n, T, beyond_next=True, one_launch_units=tc.chol_async_grid())
+    split = sched == "fork_join_lookahead" and T > tc.CHOL_BLOCK and rest_flops > 0
+    tc.chol_timing_enable(["update_rest"] if split else
                           ["update"] if sched.startswith("fork_join") else ["persistent"])
     torch.cuda.synchronize()
     t_start.record(st)
@@ -719,7 +730,7 @@ def main():
     flops = n ** 3 / 3
     value = flops / (ms_step * 1e-3) / 1e12
 
-    if sched == "fork_join_lookahead":
+    if split:
         # the bulk of each step's update: one interval per step (its pool
         # launch on the second stream and that launch's tail on the caller's
         # stream share one unit counter), one step at a time, so the summed
@@ -729,10 +740,11 @@ def main():
                   "caller's stream behind that chain, on one unit counter; timed from the first's start to the "
                   "later end)")
         kms, kcount = launches["update_rest"]
-        kflops = update_flops(n, T, beyond_next=True) * K
+        kflops = rest_flops * K
     elif sched.startswith("fork_join"):
         kernel = {"fork_join": "tc_fj_update (collapsed SYRK+GEMM trailing update, one launch per step)",
                   "fork_join_naive": "tc_fj_update_naive (trailing update parallel over tile rows, one launch per step)",
+                  "fork_join_lookahead": "tc_fj_update_range (SYRK+GEMM trailing update, one launch per step)",
                   }[sched]
         kms, kcount = launches["update"]
         kflops = update_flops(n, T) * K  # over the K timed factorizations

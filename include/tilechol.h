@@ -91,8 +91,10 @@ enum {
    * the rest (on a second stream the library keeps per host thread and
    * device), so the panel of step J+1 is factored while the rest of step J's
    * update runs.  Events keep every block's updates in step order; the
-   * factor is bit-identical to the other schedules.  The call stays ordered
-   * on the caller's stream. */
+   * factor is bit-identical to the other schedules.  Steps whose trailing
+   * update fits on the device at once, and every step of tiles of at most
+   * CHOL_BLOCK rows, run it as one launch as in CHOL_SCHED_FORK_JOIN.  The
+   * call stays ordered on the caller's stream. */
   CHOL_SCHED_FORK_JOIN_LOOKAHEAD = 4,
   /* The tile DAG as a HIP graph (the runtime-managed analogue of the
    * paper's task dependencies): the fork-join launches are graph nodes, the
@@ -517,8 +519,8 @@ int64_t chol_async_grid(void);
  * each step of CHOL_SCHED_FORK_JOIN_LOOKAHEAD (the columns beyond J+1: one
  * interval per step, from its launch on the second stream to the later of
  * that launch's end and the end of its tail launch on the call's stream,
- * which shares its unit counter; its column-(J+1) launches count under bit
- * CHOL_UNIT_UPDATE); 0 turns timing off.  While enabled on
+ * which shares its unit counter; its column-(J+1) launches, and the steps it
+ * runs as one launch, count under bit CHOL_UNIT_UPDATE); 0 turns timing off.  While enabled on
  * the calling thread, each selected launch chol_factor enqueues is
  * bracketed by a pair of HIP events on the call's stream (events are
  * created on first use and reused; no device memory is allocated; each pair
