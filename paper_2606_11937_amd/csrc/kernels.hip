@@ -126,6 +126,20 @@ __device__ __forceinline__ void tc_run_trsm_half(double* A, int64_t lda, const T
   tc_trsm_rows(A + r0 * lda + c0, A + c0 * lda + c0, lda, mr < 64 ? mr : 64, tc_rows(g, J, s), sm);
 }
 
+// Whether a product unit is a full diagonal block that tc_syrk_block takes.
+__device__ __forceinline__ bool tc_syrk_fits(bool diag, int mr, int kd) {
+  return diag && mr == 128 && kd > 0 && (kd & 15) == 0;
+}
+
+// C -= PA PB^T for a product unit, whichever body takes it.
+__device__ __forceinline__ void tc_product_block(double* C, const double* PA, const double* PB, int64_t lda, int mr,
+                                                 int mc, int kd, bool diag, TcSmem& sm) {
+  if (tc_syrk_fits(diag, mr, kd))
+    (void)tc_syrk_block<false>(C, PA, lda, kd, sm.upd, sm.potrf);
+  else
+    tc_update_block(C, PA, PB, lda, mr, mc, kd, diag, sm.upd);
+}
+
 // UPDATE(J, (I, a), (K, b)): K-depth the whole tile column J.
 __device__ __forceinline__ void tc_run_update(double* A, int64_t lda, const TcGeom& g, const TcUnit& u, TcUpdSmem& sm) {
   const int64_t ri = tc_row0(g, u.I, u.a);
@@ -148,15 +162,15 @@ __device__ __forceinline__ void tc_run_panel(double* A, int64_t lda, const TcGeo
 // UPDATE and PANEL units through one call of the block product, so that the
 // persistent kernels, which run both kinds, hold one copy of its code.
 __device__ __forceinline__ void tc_run_product(double* A, int64_t lda, const TcGeom& g, const TcUnit& u,
-                                               TcUpdSmem& sm) {
+                                               TcSmem& sm) {
   const bool up = u.kind == TC_UNIT_UPDATE;
   const int64_t ri = tc_row0(g, u.I, u.a);
   const int64_t rk = up ? tc_row0(g, u.K, u.b) : tc_row0(g, u.J, u.b);
   const int64_t ck = up ? (int64_t)u.J * g.T : tc_row0(g, u.J, u.K);
   const int mc = up ? tc_rows(g, u.K, u.b) : tc_rows(g, u.J, u.b);
   const int kd = up ? (int)tc_tdim(g, u.J) : tc_rows(g, u.J, u.K);
-  tc_update_block(A + ri * lda + rk, A + ri * lda + ck, A + rk * lda + ck, lda, tc_rows(g, u.I, u.a), mc, kd,
-                  ri == rk, sm);
+  tc_product_block(A + ri * lda + rk, A + ri * lda + ck, A + rk * lda + ck, lda, tc_rows(g, u.I, u.a), mc, kd,
+                   ri == rk, sm);
 }
 
 // ---------------------------------------------------------- fork-join kernels
@@ -181,6 +195,26 @@ union alignas(512) TcUpdPotrfSmem {
   TcPotrfSmem potrf;
 };
 
+// The head of such a launch: the update of diagonal block (r0, r0) with the
+// kd columns from c0 on, then its POTRF, in one pass over the block where it
+// is a full one.  Alone on a CU, K = 128: 20.2 + 22.2 us as two bodies.
+__device__ __forceinline__ void tc_run_update_potrf(double* A, int64_t lda, const TcGeom& g, int32_t J, int32_t s,
+                                                    int64_t c0, int kd, TcWsHeader* h, TcUpdPotrfSmem& sm) {
+  const int64_t d0 = tc_row0(g, J, s);
+  const int td = tc_rows(g, J, s);
+  double* D = A + d0 * lda + d0;
+  const double* P = A + d0 * lda + c0;
+  int bad;
+  if (tc_syrk_fits(true, td, kd)) {
+    bad = tc_syrk_block<true>(D, P, lda, kd, sm.upd, sm.potrf);
+  } else {
+    tc_update_block(D, P, P, lda, td, td, kd, true, sm.upd);
+    __syncthreads();
+    bad = tc_potrf_tile(D, lda, td, sm.potrf);
+  }
+  if (bad >= 0 && tc_tid() == 0) tc_report_fail(h, 1, d0 + bad + 1);
+}
+
 // The TRSM launch asks for as much LDS as the panel launch that follows it.
 // Under the lookahead a pool workgroup of the bulk update may be placed above
 // a TRSM workgroup and stay for the whole bulk: the hole the TRSM leaves then
@@ -204,12 +238,11 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_panel(double* A, int64_t 
                                                              TcWs ws) {
   __shared__ TcUpdPotrfSmem sm;
   if (tc_err_set(ws.hdr) || ws.noop) return;
-  const TcUnit u = tc_decode_panel(g, J, s, blockIdx.x);
-  tc_run_panel(A, lda, g, u, sm.upd);
   if (blockIdx.x == 0) {  // the update of diagonal block gid(J, s+1)
-    __syncthreads();
-    tc_run_potrf(A, lda, g, J, s + 1, ws.hdr, sm.potrf);
+    tc_run_update_potrf(A, lda, g, J, s + 1, tc_row0(g, J, s), tc_rows(g, J, s), ws.hdr, sm);
+    return;
   }
+  tc_run_panel(A, lda, g, tc_decode_panel(g, J, s, blockIdx.x), sm.upd);
 }
 
 // Panel update without the fused POTRF (the naive variant launches every
@@ -225,12 +258,11 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_panel_only(double* A, int
 __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_update(double* A, int64_t lda, TcGeom g, int32_t J, TcWs ws) {
   __shared__ TcUpdPotrfSmem sm;
   if (tc_err_set(ws.hdr) || ws.noop) return;
-  const TcUnit u = tc_decode_trailing(g, J, J, blockIdx.x);
-  tc_run_update(A, lda, g, u, sm.upd);
   if (blockIdx.x == 0) {  // the last update of diagonal block gid(J+1, 0)
-    __syncthreads();
-    tc_run_potrf(A, lda, g, J + 1, 0, ws.hdr, sm.potrf);
+    tc_run_update_potrf(A, lda, g, J + 1, 0, (int64_t)J * g.T, (int)tc_tdim(g, J), ws.hdr, sm);
+    return;
   }
+  tc_run_update(A, lda, g, tc_decode_trailing(g, J, J, blockIdx.x), sm.upd);
 }
 
 // Naive fork-join (the paper's first variant): the trailing update is
@@ -262,12 +294,11 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_update_range(double* A, i
                                                                     TcWs ws, int64_t first) {
   __shared__ TcUpdPotrfSmem sm;
   if (tc_err_set(ws.hdr) || ws.noop) return;
-  const TcUnit u = tc_decode_trailing(g, J, J, first + blockIdx.x);
-  tc_run_update(A, lda, g, u, sm.upd);
   if (first == 0 && blockIdx.x == 0) {  // the last update of diagonal block gid(J+1, 0)
-    __syncthreads();
-    tc_run_potrf(A, lda, g, J + 1, 0, ws.hdr, sm.potrf);
+    tc_run_update_potrf(A, lda, g, J + 1, 0, (int64_t)J * g.T, (int)tc_tdim(g, J), ws.hdr, sm);
+    return;
   }
+  tc_run_update(A, lda, g, tc_decode_trailing(g, J, J, first + blockIdx.x), sm.upd);
 }
 
 // The bulk of step J's update (units [first, first + count) of the launch
@@ -535,7 +566,7 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     if (ws.noop) {
       // measurement mode: the schedule's own cost only
     } else if (u.kind == TC_UNIT_UPDATE || u.kind == TC_UNIT_PANEL) {
-      tc_run_product(A, lda, cg, u, sm.upd);
+      tc_run_product(A, lda, cg, u, sm);
     } else if (u.kind == TC_UNIT_TRSM) {
       tc_run_trsm(A, lda, cg, u.J, u.K, u.I, u.a, sm.trsm);
     } else {
@@ -997,7 +1028,7 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
                                          tc_rows(cg, u.I, u.a), tc_rows(cg, u.K, u.b), (int)tc_tdim(cg, u.J),
                                          ri == rk, sm.f.upd);
       } else if (u.kind == TC_UNIT_UPDATE || u.kind == TC_UNIT_PANEL) {
-        tc_run_product(A, lda, cg, u, sm.f.upd);
+        tc_run_product(A, lda, cg, u, sm.f);
       } else if (u.kind == TC_UNIT_TRSM) {
         tc_run_trsm(A, lda, cg, u.J, u.K, u.I, u.a, sm.f.trsm);
         if (prec == TC_PREC_FP32 && u.K == tc_sb(cg, u.J) - 1 && u.I > u.J) {

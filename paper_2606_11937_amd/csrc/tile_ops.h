@@ -794,11 +794,12 @@ __device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const doubl
 // In step 3 wave 0 updates only block (b+1, b+1), straight from the registers
 // of its own substitution, and then factors it (step 1 of b+1) while waves
 // 1..3 update the other blocks.
-// In-kernel time of one workgroup with a 128 x 128 tile: 24.0 us (43.0 us
+// In-kernel time of one workgroup with a 128 x 128 tile: 22.2 us (43.0 us
 // with two lane reads per broadcast, the library square root, a substitution
-// with one row per thread and predicated loads).  What bounds it: the 16
-// pivots of a diagonal block are one wave's chain of about 210 cycles each,
-// 27000 of the 57000 cycles; the copy in and out takes 12000.
+// with one row per thread and predicated loads; 24.0 us with the whole tile
+// copied in before the first pivot and out after the last).  What bounds it:
+// the 16 pivots of a diagonal block are one wave's chain of about 210 cycles
+// each, 27000 of the 53000 cycles.
 // A pivot d <= 0 or NaN stops the factorization: returns the 0-based in-tile
 // column, else -1 (the tile is then left partly factored).
 // ---------------------------------------------------------------------------
@@ -810,68 +811,104 @@ struct alignas(16) TcPotrfSmem {
 
 __device__ __forceinline__ int tc_pk(int i, int j) { return i * (i + 1) / 2 + j; }
 
-// Lower triangle of D (rows and columns < td) into the packed blocks, or
-// (OUT) back into D.  Pass k moves blocks 2 k and 2 k + 1 (waves 0-1 and 2-3,
-// 16 rows x 8 slots each), so the block of a pass is uniform per wave; all
-// loads are issued before the first store.  A full tile moves 16-byte pairs:
-// those of a diagonal block reach above the diagonal on the way in (entries
-// that never feed one on or below it) and are masked on the way out.  A
-// ragged tile reads from clamped positions on or below the diagonal and
-// selects afterwards (zero past td), so no load waits in a branch of its own.
-template <bool OUT>
-__device__ __forceinline__ void tc_pk_copy(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm) {
-  const int tid = tc_tid();
-  const int nbk = (td + 15) >> 4;
-  const int nblk = nbk * (nbk + 1) / 2;
-  const int hi = tc_uniform((int32_t)(tid >> 7));
-  const int r = (tid >> 3) & 15, s = tid & 7;
-  double* const lrow = &sm.blk[0][0] + r * 16 + ((s ^ (r & 7)) << 1);
-  auto pos = [&](int p, int& bi, int& bj) {
-    bi = 0;
+// The packed blocks move in halves of 8 rows x 8 slots, one 16-byte pair per
+// lane.  A full tile moves whole pairs: those of a diagonal block reach above
+// the diagonal on the way in (entries that never feed one on or below it) and
+// are masked on the way out.  A ragged tile reads from clamped positions on
+// or below the diagonal and selects when it writes to LDS (zero past td), so
+// all loads are in flight together.
+__device__ __forceinline__ tc_d2 tc_half_ld(const double* __restrict__ D, int64_t lda, int td, int R, int C) {
+  if (td == 128) return *(const tc_d2*)(D + (int64_t)R * lda + C);
+  const int Rc = R < td ? R : td - 1, C0 = C < Rc ? C : Rc, C1 = C + 1 < Rc ? C + 1 : Rc;
+  tc_d2 v;
+  v.x = D[(int64_t)Rc * lda + C0];
+  v.y = D[(int64_t)Rc * lda + C1];
+  return v;
+}
+__device__ __forceinline__ double* tc_half_at(TcPotrfSmem& sm, int p, int half, int lane) {
+  const int r = 8 * half + (lane >> 3), s = lane & 7;
+  return sm.blk[p] + r * 16 + ((s ^ (r & 7)) << 1);
+}
+__device__ __forceinline__ void tc_half_put(TcPotrfSmem& sm, int p, int half, int lane, int td, int R, int C,
+                                            tc_d2 v) {
+  tc_d2a16 x;
+  x.x = td == 128 || (R < td && C <= R) ? v.x : 0.0;
+  x.y = td == 128 || (R < td && C + 1 <= R) ? v.y : 0.0;
+  *(tc_d2a16*)tc_half_at(sm, p, half, lane) = x;
+}
+
+// Lower triangle of D into the packed blocks: wave 0 only the first diagonal
+// block, which it factors while waves 1 .. 3 load the other 35.
+__device__ __forceinline__ void tc_pk_load(const double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm, int wu,
+                                           int lane) {
+  const int r8 = lane >> 3, c2 = 2 * (lane & 7);
+  if (wu == 0) {
+    const tc_d2 a = tc_half_ld(D, lda, td, r8, c2), b = tc_half_ld(D, lda, td, 8 + r8, c2);
+    tc_half_put(sm, 0, 0, lane, td, r8, c2, a);
+    tc_half_put(sm, 0, 1, lane, td, 8 + r8, c2, b);
+    tc_wave_sync();
+    return;
+  }
+  // halves h = wu - 1 + 3 k of blocks 1 + h / 2
+  auto at = [&](int h, int& R, int& C) {
+    const int p = 1 + (h >> 1);
+    int bi = 1;
 #pragma unroll
-    for (int q = 1; q < 8; ++q) bi += p >= q * (q + 1) / 2;
-    bj = p - bi * (bi + 1) / 2;
+    for (int q = 2; q < 8; ++q) bi += p >= q * (q + 1) / 2;
+    R = 16 * bi + 8 * (h & 1) + r8;
+    C = 16 * (p - bi * (bi + 1) / 2) + c2;
   };
-  if constexpr (OUT) {
+  if (td == 128) {
+    tc_d2 v[24];
 #pragma unroll
-    for (int k = 0; k < 18; ++k) {
-      const int p = 2 * k + hi;
-      if (p >= nblk) break;
-      int bi, bj;
-      pos(p, bi, bj);
-      const int R = 16 * bi + r, C = 16 * bj + 2 * s;
-      double* g = D + (int64_t)R * lda + C;
-      const tc_d2a16 x = *(const tc_d2a16*)(lrow + p * 256);
-      if (td == 128 && bi != bj) {
-        *(tc_d2*)g = tc_d2{x.x, x.y};
-      } else if (R < td) {
-        if (C <= R) g[0] = x.x;
-        if (C + 1 <= R) g[1] = x.y;
-      }
-    }
-  } else {
-    tc_d2 v[18];
-#pragma unroll
-    for (int k = 0; k < 18; ++k) {
-      int bi, bj;
-      pos(2 * k + hi, bi, bj);
-      const int R = 16 * bi + r, C = 16 * bj + 2 * s;
-      if (td == 128) {
-        v[k] = *(const tc_d2*)(D + (int64_t)R * lda + C);
-      } else {
-        const int Rc = R < td ? R : td - 1, C0 = C < Rc ? C : Rc, C1 = C + 1 < Rc ? C + 1 : Rc;
-        v[k].x = D[(int64_t)Rc * lda + C0];
-        v[k].y = D[(int64_t)Rc * lda + C1];
-        v[k].x = R < td && C <= R ? v[k].x : 0.0;
-        v[k].y = R < td && C + 1 <= R ? v[k].y : 0.0;
-      }
+    for (int k = 0; k < 24; ++k) {
+      int R, C;
+      at(wu - 1 + 3 * k < 70 ? wu - 1 + 3 * k : 69, R, C);
+      v[k] = *(const tc_d2*)(D + (int64_t)R * lda + C);
     }
 #pragma unroll
-    for (int k = 0; k < 18; ++k) {
-      tc_d2a16 x;
-      x.x = v[k].x;
-      x.y = v[k].y;
-      *(tc_d2a16*)(lrow + (2 * k + hi) * 256) = x;
+    for (int k = 0; k < 24; ++k) {
+      const int h = wu - 1 + 3 * k < 70 ? wu - 1 + 3 * k : 69;
+      tc_half_put(sm, 1 + (h >> 1), h & 1, lane, 128, 0, 0, v[k]);
+    }
+  } else {  // six at a time
+    const int nbk = (td + 15) >> 4;
+    const int nh = nbk * (nbk + 1) - 2;
+#pragma unroll 1
+    for (int h0 = wu - 1; h0 < nh; h0 += 18) {
+      tc_d2 v[6];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        int R, C;
+        at(h0 + 3 * k < nh ? h0 + 3 * k : nh - 1, R, C);
+        v[k] = tc_half_ld(D, lda, td, R, C);
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const int h = h0 + 3 * k < nh ? h0 + 3 * k : nh - 1;
+        int R, C;
+        at(h, R, C);
+        tc_half_put(sm, 1 + (h >> 1), h & 1, lane, td, R, C, v[k]);
+      }
+    }
+  }
+}
+
+// Block column c of the factor back to D, halves wv, wv + nw, ...
+__device__ __forceinline__ void tc_pk_store_col(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm, int c,
+                                                int nbk, int wv, int nw, int lane) {
+  const int r8 = lane >> 3, c2 = 2 * (lane & 7);
+#pragma unroll 1
+  for (int h = wv; h < 2 * (nbk - c); h += nw) {
+    const int i = c + (h >> 1);
+    const int R = 16 * i + 8 * (h & 1) + r8, C = 16 * c + c2;
+    double* g = D + (int64_t)R * lda + C;
+    const tc_d2a16 x = *(const tc_d2a16*)tc_half_at(sm, tc_pk(i, c), h & 1, lane);
+    if (td == 128 && i != c) {
+      *(tc_d2*)g = tc_d2{x.x, x.y};
+    } else if (R < td) {
+      if (C <= R) g[0] = x.x;
+      if (C + 1 <= R) g[1] = x.y;
     }
   }
 }
@@ -953,15 +990,17 @@ __device__ __forceinline__ void tc_pk_diag(TcPotrfSmem& sm, int b, int nb, int c
   if (lane == 0 && bad >= 0) sm.fail = c0 + bad;
 }
 
-__device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda, int td_in, TcPotrfSmem& sm) {
+// LOAD: the tile is read from D; otherwise it is in sm.blk already (complete
+// for every thread).
+template <bool LOAD>
+__device__ __forceinline__ int tc_potrf_body(double* __restrict__ D, int64_t lda, int td_in, TcPotrfSmem& sm) {
   const int td = tc_uniform((int32_t)td_in);
   const int tid = tc_tid(), lane = tid & 63, w = tid >> 6;
   const int wu = tc_uniform((int32_t)w);
   const int r16 = lane & 15, s4 = lane >> 4;
   const int nbk = (td + 15) >> 4;
-  tc_pk_copy<false>(D, lda, td, sm);
   if (tid == 0) sm.fail = -1;
-  __syncthreads();
+  if constexpr (LOAD) tc_pk_load(D, lda, td, sm, wu, lane);
   if (wu == 0) tc_pk_diag(sm, 0, td < 16 ? td : 16, 0);
   __syncthreads();
   int fail = tc_uniform((int32_t)sm.fail);
@@ -1040,10 +1079,145 @@ __device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda
           tc_acc_put(cb + (j - 1) * 256, lane, 16, tc_nt16(xi, yj, cj));
         }
       }
+      // block column b - 2, final since step b - 2, goes back to D here,
+      // where these waves wait for wave 0 anyway
+      if (b >= 2) tc_pk_store_col(D, lda, td, sm, b - 2, nbk, wu - 1, 3, lane);
     }
     __syncthreads();
     fail = tc_uniform((int32_t)sm.fail);
   }
-  tc_pk_copy<true>(D, lda, td, sm);
-  return fail;
+  if (fail >= 0) return fail;  // (the tile is left partly factored)
+  for (int c = nbk > 3 ? nbk - 3 : 0; c < nbk; ++c) tc_pk_store_col(D, lda, td, sm, c, nbk, wu, 4, lane);
+  return -1;
+}
+
+__device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm) {
+  return tc_potrf_body<true>(D, lda, td, sm);
+}
+
+// ---------------------------------------------------------------------------
+// SYRK update of a full 128 x 128 diagonal block, C -= P P^T for P of 128
+// rows and kd columns (kd a positive multiple of 16), lower triangle only;
+// POTRF: the updated block goes to LDS instead of memory and is factored
+// there, so it is neither written nor read back in between (returns the
+// failing column or -1).
+// The general update gives each wave a 64 x 64 quadrant: on a diagonal block
+// one wave idles and two do six tiles of sixteen for nothing.  Here wave w
+// takes tile rows w and 7 - w of the lower triangle's 36 16 x 16 tiles, nine
+// tiles each, 36 MFMAs per 16-wide k chunk instead of 64.  Only one operand is
+// staged (16 KB a chunk), so four stages fit where the general update has two
+// and loads run three chunks ahead.  C is read behind the last chunk's
+// products.  Each entry's products are summed in the order of the general
+// update, so the bits are the same.
+// Alone on a CU, kd = 128: 13.1 us (20.2 us as a general update; 18400 cycles
+// of MFMAs, 7.7 us); with the POTRF 32.0 us (20.2 + 22.2 us as two bodies).
+// ---------------------------------------------------------------------------
+template <bool POTRF>
+__device__ __forceinline__ int tc_syrk_block(double* __restrict__ C, const double* __restrict__ P, int64_t lda, int kd,
+                                             TcUpdSmem& sm, TcPotrfSmem& pm) {
+  const int tid = tc_tid(), lane = tid & 63;
+  const int wu = tc_uniform((int32_t)(tid >> 6));
+  const int r16 = lane & 15, s4 = lane >> 4;
+  double* const st0 = &sm.tile[0][0][0];
+  // staging: wave w fetches rows 32 w .. 32 w + 31, eight a load
+  const double* src = (const double*)tc_uniform((int64_t)P);
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)(128 * tc_uniform(lda) * 8), 0x00020000);
+  const int rl0 = wu * 32 + (lane >> 3);
+  const unsigned vof0 = (unsigned)(rl0 * lda * 8 + 16 * ((lane & 7) ^ tc_swz(rl0)));
+  const unsigned rowstep = (unsigned)(8 * lda * 8);
+  auto stage = [&](int c) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc,
+          (tc_lds_void*)((char __attribute__((address_space(3)))*)(tc_lds_void*)st0 + (c & 3) * 16384 +
+                         (wu * 4 + q) * 1024),
+          16, vof0 + q * rowstep, (unsigned)(c * 128), 0, 0);
+  };
+  auto frag = [&](int c, int i) { return tc_frag_get(st0 + (c & 3) * 2048 + i * 256, r16, s4, 16); };
+  const int nch = kd >> 4;
+  const int ra = 7 - wu;  // the wave's tile rows: ra (tiles 0 .. ra) and wu (tiles 0 .. wu)
+  tc_v4d acc[8], acd[4];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = tc_v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acd[j] = tc_v4d{0.0, 0.0, 0.0, 0.0};
+  auto products = [&](int c) {
+    const tc_q4 fa = frag(c, ra), fd = frag(c, wu);
+    tc_q4 f[2];
+    f[0] = frag(c, 0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j <= ra) {
+        if (j < 7) f[(j + 1) & 1] = frag(c, j + 1);  // (one more than the last tile needs, at most)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[j] = tc_mfma(tc_el(fa, m), tc_el(f[j & 1], m), acc[j]);
+        if (j < 4 && j <= wu) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m) acd[j & 3] = tc_mfma(tc_el(fd, m), tc_el(f[j & 1], m), acd[j & 3]);
+        }
+      }
+    }
+  };
+  // chunk c has landed when at most the loads of c + 1 and c + 2 are
+  // outstanding (s_waitcnt encodings: 0x0F78 = vmcnt(8), 0x0F74 = vmcnt(4),
+  // 0x0F70 = vmcnt(0)); the barrier behind the wait publishes it and, because
+  // every wave has read chunk c - 1 by then, frees that chunk's stage
+  auto publish = [] {
+    asm volatile("" ::: "memory");  // no LDS read moves across the barrier
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  stage(0);
+  if (nch > 1) stage(1);
+  if (nch > 2) stage(2);
+  for (int c = 0; c < nch - 1; ++c) {
+    if (c + 2 < nch) __builtin_amdgcn_s_waitcnt(0x0F78); else __builtin_amdgcn_s_waitcnt(0x0F74);
+    publish();
+    if (c + 3 < nch) stage(c + 3);
+    products(c);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  publish();
+  tc_v4d cv[8], cd[4];
+  auto cload = [&](int i, int j) {
+    const double* p = C + (int64_t)(16 * i + s4) * lda + 16 * j + r16;
+    tc_v4d v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = p[(int64_t)(4 * q) * lda];
+    return v;
+  };
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (j <= ra) cv[j] = cload(ra, j);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (j <= wu) cd[j] = cload(wu, j);
+  products(nch - 1);
+  if constexpr (POTRF) {
+    __syncthreads();  // every wave is done with the stages, which the packed blocks overlay
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j <= ra) tc_acc_put(pm.blk[tc_pk(ra, j)], lane, 16, cv[j] - acc[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j <= wu) tc_acc_put(pm.blk[tc_pk(wu, j)], lane, 16, cd[j] - acd[j]);
+    __syncthreads();
+    return tc_potrf_body<false>(C, lda, 128, pm);
+  } else {
+    auto cstore = [&](int i, int j, tc_v4d v) {
+      double* p = C + (int64_t)(16 * i + s4) * lda + 16 * j + r16;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i > j || 4 * q + s4 >= r16) p[(int64_t)(4 * q) * lda] = v[q];
+    };
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j <= ra) cstore(ra, j, cv[j] - acc[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j <= wu) cstore(wu, j, cd[j] - acd[j]);
+    return -1;
+  }
 }

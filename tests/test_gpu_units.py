@@ -2,7 +2,9 @@
 
 A pivot below 2^-700 or not finite takes the plain form of the 16 x 16
 diagonal factorization, every other one the fast form; ragged tiles take the
-clamped loads and masked stores.  Tolerances, fixed in advance:
+clamped loads and masked stores; a full diagonal block with an update depth
+that is a multiple of 16 takes its update and POTRF in one body (T = 136 has
+full blocks of a depth that is not).  Tolerances, fixed in advance:
   scaling   A 4^k has the factor 2^k L.  Nothing underflows at the scales
             used, so the two factors are factorizations of the same matrix by
             the same operations up to one rounding of a pivot's reciprocal;
@@ -65,7 +67,7 @@ def test_failing_pivot_position(tc, k, value):
 
 
 @pytest.mark.parametrize("T,n", [(1, 5), (3, 10), (15, 40), (16, 33), (17, 60), (100, 260), (127, 300), (128, 129),
-                                 (128, 143), (128, 192), (128, 193), (129, 300)])
+                                 (128, 143), (128, 192), (128, 193), (129, 300), (136, 420), (144, 420), (256, 700)])
 def test_ragged_tiles(tc, T, n):
     A = inputs.gg_plus_identity(n, seed=T)
     ref, info = oracle.potrf(A)
