@@ -197,7 +197,6 @@ int chol_solve(const double* L, int64_t n, int64_t lda, int64_t T, double* B, in
   if (work == nullptr) return bad(8);
   if (work_bytes < tc_solve_ws_bytes(n, nrhs, false)) return bad(9, CHOL_EWORKSPACE);
   hipStream_t st = (hipStream_t)stream;
-  if (tc_solve_status_reset(work, st) != 0) return CHOL_EDEVICE;
   return tc_launch_solve(L, n, lda, T, B, nrhs, ldb, work, st, wait_ticks()) == 0 ? CHOL_OK : CHOL_EDEVICE;
 }
 

@@ -58,9 +58,10 @@ int64_t tc_sync_grid_size();
 // tickets, done counters and a status word, then the two sweeps' payloads
 // (inv: the sweeps with inverted diagonal blocks).
 int64_t tc_solve_ws_bytes(int64_t n, int64_t nrhs, bool inv);
-// The status word: cleared by tc_solve_status_reset (enqueued), set when a
-// sweep's dependency wait runs out, kept by the launches below (which clear
-// only their counters) until the next reset; tc_solve_status synchronises
+// The status word: cleared by tc_solve_status_reset (enqueued) and at the
+// start of tc_launch_solve, set when a sweep's dependency wait runs out, kept
+// by the other launches below (which clear only their counters) until the
+// next reset; tc_solve_status synchronises
 // `st` and reads it; tc_solve_status_offset is its byte offset.
 int tc_solve_status_reset(void* work, hipStream_t st);
 int tc_solve_status(const void* work, hipStream_t st, int32_t* error);

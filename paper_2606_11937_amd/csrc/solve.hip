@@ -62,6 +62,207 @@ __device__ __forceinline__ double sv_readlane(double v, int l) {
   return __builtin_bit_cast(double, (int64_t)(((uint64_t)hi << 32) | lo));
 }
 
+// ------------------------------------------------ row-broadcast operands
+// The chain of a block step, its dot with the neighbour's solution and its
+// 64 x 64 substitution, runs on one wave with one row per lane.  An FP64
+// multiply-add can take one operand from lane k of each 16-lane row
+// (row_newbcast:k), so values held 16 to a row need no lane reads and no LDS:
+// 6 cycles per term where a broadcast through LDS and an FMA took about 20,
+// and 17.5 cycles per dependent step of the substitution (its two wait states
+// included) where two lane reads and an FMA take 26.  Assembly, because the
+// compiler emits a move per broadcast; every block waits out the vector write
+// in front of it itself, and the whole wave is active.
+
+// d[k % 4] += c[K0 + k] * (y of lane k of the row), k = 0 .. 15 ascending
+template <int K0>
+__device__ __forceinline__ void sv_dot16(double (&d)[4], const double (&c)[SV_NB], double y) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c0] row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %[y], %[c1] row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %[y], %[c2] row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %[y], %[c3] row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c4] row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %[y], %[c5] row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %[y], %[c6] row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %[y], %[c7] row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c8] row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %[y], %[c9] row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %[y], %[c10] row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %[y], %[c11] row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c12] row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %[y], %[c13] row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %[y], %[c14] row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %[y], %[c15] row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
+      : "+&v"(d[0]), "+&v"(d[1]), "+&v"(d[2]), "+&v"(d[3])
+      : [y] "v"(y), [c0] "v"(c[K0 + 0]), [c1] "v"(c[K0 + 1]), [c2] "v"(c[K0 + 2]), [c3] "v"(c[K0 + 3]), [c4] "v"(c[K0 + 4]), [c5]
+        "v"(c[K0 + 5]), [c6] "v"(c[K0 + 6]), [c7] "v"(c[K0 + 7]), [c8] "v"(c[K0 + 8]), [c9] "v"(c[K0 + 9]), [c10]
+        "v"(c[K0 + 10]), [c11] "v"(c[K0 + 11]), [c12] "v"(c[K0 + 12]), [c13] "v"(c[K0 + 13]), [c14] "v"(c[K0 + 14]),
+        [c15] "v"(c[K0 + 15]));
+}
+// Steps of the substitution inside 16-row group G (the lanes of row G only):
+// v -= c[16 G + i] * (v of lane i of the row), i ascending or descending.
+template <int G>
+__device__ __forceinline__ double sv_group_up(double v, const double (&c)[SV_NB]) {
+  constexpr int K0 = 16 * G;
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c0] row_newbcast:0 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c1] row_newbcast:1 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c2] row_newbcast:2 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c3] row_newbcast:3 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c4] row_newbcast:4 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c5] row_newbcast:5 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c6] row_newbcast:6 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c7] row_newbcast:7 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c8] row_newbcast:8 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c9] row_newbcast:9 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c10] row_newbcast:10 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c11] row_newbcast:11 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c12] row_newbcast:12 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c13] row_newbcast:13 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c14] row_newbcast:14 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c15] row_newbcast:15 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+&v"(v)
+      : [m] "n"(1 << G), [c0] "v"(c[K0 + 0]), [c1] "v"(c[K0 + 1]), [c2] "v"(c[K0 + 2]), [c3] "v"(c[K0 + 3]), [c4] "v"(c[K0 + 4]), [c5]
+        "v"(c[K0 + 5]), [c6] "v"(c[K0 + 6]), [c7] "v"(c[K0 + 7]), [c8] "v"(c[K0 + 8]), [c9] "v"(c[K0 + 9]), [c10]
+        "v"(c[K0 + 10]), [c11] "v"(c[K0 + 11]), [c12] "v"(c[K0 + 12]), [c13] "v"(c[K0 + 13]), [c14] "v"(c[K0 + 14]),
+        [c15] "v"(c[K0 + 15]));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ double sv_group_down(double v, const double (&c)[SV_NB]) {
+  constexpr int K0 = 16 * G;
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c15] row_newbcast:15 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c14] row_newbcast:14 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c13] row_newbcast:13 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c12] row_newbcast:12 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c11] row_newbcast:11 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c10] row_newbcast:10 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c9] row_newbcast:9 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c8] row_newbcast:8 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c7] row_newbcast:7 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c6] row_newbcast:6 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c5] row_newbcast:5 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c4] row_newbcast:4 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c3] row_newbcast:3 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c2] row_newbcast:2 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c1] row_newbcast:1 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %[c0] row_newbcast:0 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+&v"(v)
+      : [m] "n"(1 << G), [c0] "v"(c[K0 + 0]), [c1] "v"(c[K0 + 1]), [c2] "v"(c[K0 + 2]), [c3] "v"(c[K0 + 3]), [c4] "v"(c[K0 + 4]), [c5]
+        "v"(c[K0 + 5]), [c6] "v"(c[K0 + 6]), [c7] "v"(c[K0 + 7]), [c8] "v"(c[K0 + 8]), [c9] "v"(c[K0 + 9]), [c10]
+        "v"(c[K0 + 10]), [c11] "v"(c[K0 + 11]), [c12] "v"(c[K0 + 12]), [c13] "v"(c[K0 + 13]), [c14] "v"(c[K0 + 14]),
+        [c15] "v"(c[K0 + 15]));
+  return v;
+}
+// The same products with the finished values of group G (x, one copy in every
+// row) for the lanes of the rows in MASK.
+template <int G, int MASK>
+__device__ __forceinline__ double sv_rows_up(double v, const double (&c)[SV_NB], double x) {
+  constexpr int K0 = 16 * G;
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c0] row_newbcast:0 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c1] row_newbcast:1 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c2] row_newbcast:2 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c3] row_newbcast:3 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c4] row_newbcast:4 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c5] row_newbcast:5 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c6] row_newbcast:6 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c7] row_newbcast:7 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c8] row_newbcast:8 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c9] row_newbcast:9 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c10] row_newbcast:10 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c11] row_newbcast:11 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c12] row_newbcast:12 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c13] row_newbcast:13 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c14] row_newbcast:14 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c15] row_newbcast:15 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+&v"(v)
+      : [x] "v"(x), [m] "n"(MASK), [c0] "v"(c[K0 + 0]), [c1] "v"(c[K0 + 1]), [c2] "v"(c[K0 + 2]), [c3] "v"(c[K0 + 3]), [c4] "v"(c[K0 + 4]), [c5]
+        "v"(c[K0 + 5]), [c6] "v"(c[K0 + 6]), [c7] "v"(c[K0 + 7]), [c8] "v"(c[K0 + 8]), [c9] "v"(c[K0 + 9]), [c10]
+        "v"(c[K0 + 10]), [c11] "v"(c[K0 + 11]), [c12] "v"(c[K0 + 12]), [c13] "v"(c[K0 + 13]), [c14] "v"(c[K0 + 14]),
+        [c15] "v"(c[K0 + 15]));
+  return v;
+}
+template <int G, int MASK>
+__device__ __forceinline__ double sv_rows_down(double v, const double (&c)[SV_NB], double x) {
+  constexpr int K0 = 16 * G;
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c15] row_newbcast:15 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c14] row_newbcast:14 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c13] row_newbcast:13 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c12] row_newbcast:12 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c11] row_newbcast:11 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c10] row_newbcast:10 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c9] row_newbcast:9 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c8] row_newbcast:8 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c7] row_newbcast:7 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c6] row_newbcast:6 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c5] row_newbcast:5 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c4] row_newbcast:4 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c3] row_newbcast:3 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c2] row_newbcast:2 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c1] row_newbcast:1 row_mask:%[m] bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%[x], %[c0] row_newbcast:0 row_mask:%[m] bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+&v"(v)
+      : [x] "v"(x), [m] "n"(MASK), [c0] "v"(c[K0 + 0]), [c1] "v"(c[K0 + 1]), [c2] "v"(c[K0 + 2]), [c3] "v"(c[K0 + 3]), [c4] "v"(c[K0 + 4]), [c5]
+        "v"(c[K0 + 5]), [c6] "v"(c[K0 + 6]), [c7] "v"(c[K0 + 7]), [c8] "v"(c[K0 + 8]), [c9] "v"(c[K0 + 9]), [c10]
+        "v"(c[K0 + 10]), [c11] "v"(c[K0 + 11]), [c12] "v"(c[K0 + 12]), [c13] "v"(c[K0 + 13]), [c14] "v"(c[K0 + 14]),
+        [c15] "v"(c[K0 + 15]));
+  return v;
+}
+// Row G of the wave (16 lanes) copied to all four rows.
+template <int G>
+__device__ __forceinline__ double sv_row_copy(double v) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const u2 a = __builtin_bit_cast(u2, v);
+  u2 o;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // rows {0, 0, 2, 2} and {1, 1, 3, 3}, then the low or the high pair twice
+    const auto p = __builtin_amdgcn_permlane16_swap(a[h], a[h], false, false);
+    const unsigned b = (G & 1) ? p[1] : p[0];
+    const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    o[h] = G < 2 ? q[0] : q[1];
+  }
+  return __builtin_bit_cast(double, o);
+}
+// c . y for the lane's 64 coefficients; y[t] holds entries 16 t .. 16 t + 15,
+// one copy per row.  Four partial sums over k = 4 i + r, ascending, added as
+// (d0 + d1) + (d2 + d3).
+__device__ __forceinline__ double sv_dot64(const double (&c)[SV_NB], const double (&y)[4]) {
+  double d[4] = {0.0, 0.0, 0.0, 0.0};
+  sv_dot16<0>(d, c, y[0]);
+  sv_dot16<16>(d, c, y[1]);
+  sv_dot16<32>(d, c, y[2]);
+  sv_dot16<48>(d, c, y[3]);
+  return (d[0] + d[1]) + (d[2] + d[3]);
+}
+// The substitution with a unit diagonal: lane k holds its value and its row
+// (column, backward) of the strictly lower (upper) block, zero on and past
+// the diagonal.  Each lane receives its subtractions in ascending
+// (descending) order of the column.
+__device__ __forceinline__ double sv_chain64_fwd(double v, const double (&c)[SV_NB]) {
+  v = sv_group_up<0>(v, c);
+  v = sv_rows_up<0, 0xe>(v, c, sv_row_copy<0>(v));
+  v = sv_group_up<1>(v, c);
+  v = sv_rows_up<1, 0xc>(v, c, sv_row_copy<1>(v));
+  v = sv_group_up<2>(v, c);
+  v = sv_rows_up<2, 0x8>(v, c, sv_row_copy<2>(v));
+  return sv_group_up<3>(v, c);
+}
+__device__ __forceinline__ double sv_chain64_bwd(double v, const double (&c)[SV_NB]) {
+  v = sv_group_down<3>(v, c);
+  v = sv_rows_down<3, 0x7>(v, c, sv_row_copy<3>(v));
+  v = sv_group_down<2>(v, c);
+  v = sv_rows_down<2, 0x3>(v, c, sv_row_copy<2>(v));
+  v = sv_group_down<1>(v, c);
+  v = sv_rows_down<1, 0x1>(v, c, sv_row_copy<1>(v));
+  return sv_group_down<0>(v, c);
+}
+
 // ------------------------------------------------------------ hand-off
 // The solved entries of a block reach the workgroups that fold them as data,
 // not behind a counter: the owner stores them as relaxed device-scope 64-bit
@@ -137,21 +338,99 @@ __device__ __forceinline__ bool sv_wave_wait_full(Load load, Pending pending, Sv
   }
 }
 
-// Stage the diagonal block strictly lower (zero on and above the diagonal)
-// and the reciprocals of its diagonal (every thread of the workgroup takes
-// part).  Rows past nr take a unit pivot.  rdiag is written after the
-// internal barrier: readers need one more barrier.
-__device__ __forceinline__ void sv_stage_diag(const double* __restrict__ L, int64_t lda, int64_t r0, int nr,
-                                              double (*Lbb)[SV_NB + 1], double* rdiag) {
-  for (int e = threadIdx.x; e < SV_NB * SV_NB; e += SV_THREADS) {
-    const int i = e / SV_NB, k = e % SV_NB;
-    Lbb[i][k] = (i < nr && k < i) ? L[(r0 + i) * lda + r0 + k] : 0.0;
+// A thread's share of a 64 x 64 tile of L on its way into LDS: rows
+// i0 + tid / 64 + 4 q, column j0 + tid % 64.  Rows and columns past the
+// matrix read its last ones (in bounds) and are dropped at the store, so the
+// loads are plain and all in flight together.
+__device__ __forceinline__ void sv_tile_load(const double* __restrict__ L, int64_t lda, int64_t n, int64_t i0,
+                                             int64_t j0, double (&t)[16]) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const double* p = L + (j0 + lane < n ? j0 + lane : n - 1);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int64_t r = i0 + w + 4 * q;
+    t[q] = p[(r < n ? r : n - 1) * lda];
   }
-  __syncthreads();
-  if (threadIdx.x < SV_NB) {
-    const int i = threadIdx.x;
-    rdiag[i] = i < nr ? 1.0 / L[(r0 + i) * lda + r0 + i] : 1.0;
+}
+// A tile in LDS with the coefficients of chain lane k as row k, read 16 bytes
+// at a time (a row of 66 doubles keeps the reads aligned and off each
+// other's banks).
+#define SV_TS (SV_NB + 2)
+__device__ __forceinline__ void sv_coefs(const double (*T)[SV_TS], int lane, double (&c)[SV_NB]) {
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(16)));
+#pragma unroll
+  for (int k = 0; k < SV_NB; k += 2) {
+    const d2 v = *(const d2*)&T[lane][k];
+    c[k] = v.x;
+    c[k + 1] = v.y;
   }
+}
+__device__ __forceinline__ void sv_coefs(const double (*T)[SV_TS], int lane, double scale, double (&c)[SV_NB]) {
+  sv_coefs(T, lane, c);
+#pragma unroll
+  for (int k = 0; k < SV_NB; ++k) c[k] = c[k] * scale;
+}
+// 64 consecutive doubles of memory
+__device__ __forceinline__ void sv_row_ld(const double* __restrict__ p, double (&c)[SV_NB]) {
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+  for (int k = 0; k < SV_NB; k += 2) {
+    const d2 v = *(const d2*)(p + k);
+    c[k] = v.x;
+    c[k + 1] = v.y;
+  }
+}
+// Pin register values in front of a wait (an empty statement that uses them),
+// so that the compiler does not move the LDS reads behind it.
+__device__ __forceinline__ void sv_pin(double (&c)[SV_NB]) {
+#pragma unroll
+  for (int k = 0; k < SV_NB; ++k) asm volatile("" : "+v"(c[k]));
+}
+// The chain wave's wait for block j's payload column (entries p[RC k], k < 64):
+// y[t] of lane l becomes entry 16 t + l % 16, as sv_dot64 takes it.  WIDE:
+// every poll loads the four values of each lane; otherwise one value per lane
+// is polled, a quarter of the traffic when many workgroups wait at once, and
+// copied across the rows; the block before the neighbour (not NEXT) is
+// probed first.
+template <int RC, bool WIDE, bool NEXT>
+__device__ __forceinline__ bool sv_wait_col(const double* p, double (&y)[4], int lane, SvWs* ws, int64_t wait_ticks) {
+  if constexpr (WIDE) {
+    auto load = [&] {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) y[t] = sv_pay_ld(p + (16 * t + (lane & 15)) * RC);
+    };
+    load();
+    return sv_wave_wait_full(
+        load, [&] { return sv_pending(y[0]) || sv_pending(y[1]) || sv_pending(y[2]) || sv_pending(y[3]); }, ws,
+        wait_ticks);
+  } else {
+    double v = sv_pay_ld(p + lane * RC);
+    auto load = [&] { v = sv_pay_ld(p + lane * RC); };
+    auto pend = [&] { return sv_pending(v); };
+    const bool got = NEXT ? sv_wave_wait_full(load, pend, ws, wait_ticks)
+                          : sv_wave_wait(p + (SV_NB - 1) * RC, load, pend, ws, wait_ticks);
+    y[0] = sv_row_copy<0>(v);
+    y[1] = sv_row_copy<1>(v);
+    y[2] = sv_row_copy<2>(v);
+    y[3] = sv_row_copy<3>(v);
+    return got;
+  }
+}
+
+// The diagonal block strictly lower (zero on and above the diagonal and past
+// nr) and the reciprocals of its diagonal (rows past nr take a unit pivot),
+// from a thread's tile share.
+template <class Put>
+__device__ __forceinline__ void sv_diag_put(const double (&t)[16], int nr, double* rdiag, Put put) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double piv = 1.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int i = w + 4 * q;
+    put(i, lane, (i < nr && lane < i) ? t[q] : 0.0);
+    piv = (i == lane && i < nr) ? t[q] : piv;
+  }
+  if (((lane - w) & 3) == 0) rdiag[lane] = 1.0 / piv;
 }
 
 // ------------------------------------------------- in-block substitution
@@ -163,9 +442,9 @@ __device__ __forceinline__ void sv_stage_diag(const double* __restrict__ L, int6
 // i's value, which is x_i, and every lane k subtracts (L[k][i] / L[k][k]) x_i
 // with one FMA.  The kept row is zero on and past the diagonal, so a lane's
 // value stays x_k once its own step has passed.
-// Forward runs with L_bb (lane k keeps row k), backward with L_bb^T (lane k
-// keeps column k).  This is the reference BLAS triangular solve's scaling by
-// reciprocals, done ahead of the chain.
+// This is the reference BLAS triangular solve's scaling by reciprocals, done
+// ahead of the chain.  (The inversion of the diagonal blocks runs four chains
+// a wave this way; the sweeps' single chains are sv_chain64_fwd/bwd.)
 template <int NT>
 __device__ __forceinline__ void sv_chains_fwd(double* v, const double (*Lbb)[SV_NB + 1], const double* rdiag,
                                               int lane) {
@@ -182,54 +461,46 @@ __device__ __forceinline__ void sv_chains_fwd(double* v, const double (*Lbb)[SV_
   }
 }
 
-template <int NT>
-__device__ __forceinline__ void sv_chains_bwd(double* v, const double (*Lbb)[SV_NB + 1], const double* rdiag,
-                                              int lane) {
-  const double rl = rdiag[lane];
-  double lc[SV_NB];
-#pragma unroll
-  for (int i = 0; i < SV_NB; ++i) lc[i] = Lbb[i][lane] * rl;
-#pragma unroll
-  for (int t = 0; t < NT; ++t) v[t] = v[t] * rl;
-#pragma unroll
-  for (int i = SV_NB - 1; i >= 0; --i) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) v[t] = __builtin_fma(-lc[i], sv_readlane(v[t], i), v[t]);
-  }
-}
-
 // ---------------------------------------------------------------- forward
-// y_b = L_bb^{-1} (B_b - sum_{j<b} L_bj y_j), one block per workgroup, one
-// or two right-hand sides (payload width 2).  The four waves fold the blocks
-// j <= b - 2 as their payloads arrive; then wave c (c < nc) takes
-// right-hand side c alone: it waits for y_{b-1}, subtracts the fold and
-// L_{b,b-1} y_{b-1} (the tile staged in LDS at the start), substitutes, and
-// publishes its column, so the chain step involves one wave and no
-// workgroup barrier.
+// y_b = L_bb^{-1} (B_b - sum_{j<b} L_bj y_j), one block per workgroup, up to
+// four right-hand sides.  The four waves fold the blocks j <= b - 3 as their
+// payloads arrive; then wave c (c < nc) takes right-hand side c alone: it
+// waits for y_{b-2} and subtracts L_{b,b-2} y_{b-2}, waits for y_{b-1} and
+// subtracts L_{b,b-1} y_{b-1}, substitutes, and publishes its column, so the
+// last two block steps involve one wave and no workgroup barrier.  (With
+// y_{b-2} in the fold, its probe, load, row sums and barrier took 3 us from
+// its publication to the chain wave, which started late every step: 2.4 us a
+// step, 1.6 us now.)
 // Fold layout: wave w, lane 16 rr + q covers rows 16 s + 4 w + rr (s < 4)
 // of the block and columns 16 m + q (m < 4) of every folded block, so each
 // load instruction reads four whole 128-byte row segments.  A lane
 // accumulates its 4 x 4 products of every block in block order; the 16
 // lanes of a row are then summed by a butterfly.
 // Rounding order per entry (row i, right-hand side c): the fold as above;
-// B minus it; minus L_{b,b-1} y_{b-1} as four partial sums (columns
-// k = 4 i + r, ascending) added as (d0 + d1) + (d2 + d3); then the
-// substitution (sv_chains_fwd).  The forward sweep does not write
+// B minus it; minus L_{b,b-2} y_{b-2}, then minus L_{b,b-1} y_{b-1}, each as
+// four partial sums (columns k = 4 i + r, ascending) added as
+// (d0 + d1) + (d2 + d3); then the
+// substitution (sv_chain64_fwd).  The forward sweep does not write
 // B: the backward sweep reads y_b from the payload.
 // The workgroup with ticket g (counted from the solve's first) of the
 // forward sweep; npass passes of RC columns share the launch, their blocks
 // interleaved in ticket order: ticket g is block g / npass of pass
 // g % npass, and waits only for smaller tickets of its own pass.
-template <int RC>
+// WIDE: one workgroup on a CU, with three coefficient tiles in LDS and two of
+// them in the chain wave's registers (more than 256) before its wait.
+// Otherwise two workgroups share a CU: two tiles in LDS, L_{b,b-2} read from
+// memory, the diagonal block's coefficients read behind the neighbour's
+// product.  The arithmetic is the same, and so is each column's result.
+template <int RC, bool WIDE>
 __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int64_t lda, int64_t n,
                                                const double* __restrict__ B, int64_t nc, int64_t ldb, double* Ypay,
                                                double* __restrict__ Xpay, SvWs* ws, int64_t wait_ticks, int32_t npass,
                                                int64_t pstride, int32_t g) {
   static_assert(RC >= 1 && RC <= SV_THREADS / 64, "one chain wave per right-hand side");
   __shared__ double part[SV_NB][RC + 1];
-  __shared__ double Lbb[SV_NB][SV_NB + 1];
-  __shared__ double LsubT[SV_NB][SV_NB + 1];  // L_{b,b-1}, transposed
-  __shared__ double ylds[RC][SV_NB];          // y_{b-1}, broadcast to the chain wave's lanes
+  __shared__ alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block, L_{b,b-1} and L_{b,b-2}, rows of lanes
+  __shared__ alignas(16) double Ls1[SV_NB][SV_TS];
+  __shared__ alignas(16) double Ls2[WIDE ? SV_NB : 1][SV_TS];  // (in registers, later, when not WIDE)
   __shared__ double rdiag[SV_NB];
   const int tid = threadIdx.x;
   const int32_t b = g / npass, pass = g - b * npass;
@@ -247,11 +518,21 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
   if (w >= nc && w < RC) sv_pay_st(Ypay + ((int64_t)b * SV_NB + lane) * RC + w, 0.0);
   // the chain wave's own entries of B, read before any wait
   const double bown = (w < nc && lane < nr) ? B[(r0 + lane) * ldb + w] : 0.0;
-  // staged before any wait: the diagonal block, and L_{b,b-1}
-  sv_stage_diag(L, lda, r0, nr, Lbb, rdiag);
-  for (int e = tid; e < SV_NB * SV_NB; e += SV_THREADS) {
-    const int i = e / SV_NB, k = e % SV_NB;
-    LsubT[k][i] = (b > 0 && i < nr) ? L[(r0 + i) * lda + r0 - SV_NB + k] : 0.0;
+  // staged before any wait: the diagonal block, L_{b,b-1} and L_{b,b-2}
+  {
+    double td[16], t1[16], t2[16];
+    sv_tile_load(L, lda, n, r0, r0, td);
+    if (b > 0) sv_tile_load(L, lda, n, r0, r0 - SV_NB, t1);
+    if (WIDE && b > 1) sv_tile_load(L, lda, n, r0, r0 - 2 * SV_NB, t2);
+    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[i][k] = v; });
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = w + 4 * e;
+      if (b > 0) Ls1[i][lane] = i < nr ? t1[e] : 0.0;
+      if constexpr (WIDE) {
+        if (b > 1) Ls2[i][lane] = i < nr ? t2[e] : 0.0;
+      }
+    }
   }
   int frow[4];
 #pragma unroll
@@ -282,14 +563,13 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
 #pragma unroll
       for (int c = 0; c < RC; ++c) y[m][c] = sv_pay_ld(Ypay + ((int64_t)j * SV_NB + 16 * m + q) * RC + c);
   };
-  const int32_t nfold = b > 1 ? b - 1 : 0;  // blocks 0 .. b - 2
+  const int32_t nfold = b > 2 ? b - 2 : 0;  // blocks 0 .. b - 3
   double acc[4][RC];
 #pragma unroll
   for (int s2 = 0; s2 < 4; ++s2)
 #pragma unroll
     for (int c = 0; c < RC; ++c) acc[s2][c] = 0.0;
-  // the last folded tile (block b - 2) is read before any wait: its fold
-  // runs one step before the chain step
+  // the last folded tile (block b - 3) is read before any wait
   double lt[4][4], lc[4][4], ya[4][RC];
   bool ok = true;
   if (nfold > 0) {
@@ -360,33 +640,35 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
     __builtin_amdgcn_s_setprio(3);
     const int c = w;
     double v = bown - (lane < nr ? part[lane][c] : 0.0);
-    // row `lane` of L_{b,b-1} into registers before the wait
-    double lrow[SV_NB];
-#pragma unroll
-    for (int k = 0; k < SV_NB; ++k) lrow[k] = LsubT[k][lane];
-    // keep them in registers here (an empty statement that uses them), so the
-    // compiler does not move the LDS reads behind the wait
-#pragma unroll
-    for (int k = 0; k < SV_NB; ++k) asm volatile("" : "+v"(lrow[k]));
+    double y[4], l1[SV_NB], lr[SV_NB];
+    const double rl = rdiag[lane];
     bool got = all_ok;
-    if (got && b > 0) {
-      // y_{b-1}, column c: lane k holds entry k
-      double yp = sv_pay_ld(Ypay + ((int64_t)(b - 1) * SV_NB + lane) * RC + c);
-      got = sv_wave_wait_full([&] { yp = sv_pay_ld(Ypay + ((int64_t)(b - 1) * SV_NB + lane) * RC + c); },
-                              [&] { return sv_pending(yp); }, ws, wait_ticks);
-      if (got) {
-        // L_{b,b-1} y_{b-1}: y_{b-1} through LDS (the wave's LDS operations
-        // run in order), four partial sums over k = 4 i + r, then
-        // (d0 + d1) + (d2 + d3)
-        ylds[c][lane] = yp;
-        double d[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < SV_NB; ++k) d[k & 3] = __builtin_fma(lrow[k], ylds[c][k], d[k & 3]);
-        v = v - ((d[0] + d[1]) + (d[2] + d[3]));
+    if (got && b > 1) {
+      if constexpr (WIDE) {
+        sv_coefs(Ls2, lane, l1);
+      } else {  // row `lane` of L_{b,b-2} from memory (32 lines of it per wave stay in L1)
+        const double* p = L + (r0 + (lane < nr ? lane : nr - 1)) * lda + r0 - 2 * SV_NB;
+        sv_row_ld(p, l1);
       }
+      sv_pin(l1);
+      got = sv_wait_col<RC, WIDE, false>(Ypay + (int64_t)(b - 2) * SV_NB * RC + c, y, lane, ws, wait_ticks);
+      if (got) v = v - sv_dot64(l1, y);
     }
+    // row `lane` of L_{b,b-1} (and, WIDE, of L_bb scaled by the reciprocal of
+    // its pivot) into registers before the wait for the neighbour
+    if constexpr (WIDE) {
+      sv_coefs(Lbb, lane, rl, lr);
+      sv_pin(lr);
+    }
+    if (got && b > 0) {
+      sv_coefs(Ls1, lane, l1);
+      sv_pin(l1);
+      got = sv_wait_col<RC, WIDE, true>(Ypay + (int64_t)(b - 1) * SV_NB * RC + c, y, lane, ws, wait_ticks);
+      if (got) v = v - sv_dot64(l1, y);
+    }
+    if constexpr (!WIDE) sv_coefs(Lbb, lane, rl, lr);
     if (lane >= nr) v = 0.0;
-    sv_chains_fwd<1>(&v, Lbb, rdiag, lane);
+    v = sv_chain64_fwd(v * rl, lr);
     if (got) sv_pay_st(Ypay + ((int64_t)b * SV_NB + lane) * RC + c, lane < nr ? v : 0.0);
     __builtin_amdgcn_s_setprio(0);
   }
@@ -394,29 +676,29 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
 
 // --------------------------------------------------------------- backward
 // x_b = L_bb^{-T} (y_b - sum_{j>b} L_jb^T x_j), one block per workgroup:
-// the four waves fold the blocks j >= b + 2 as their payloads arrive, then
-// wave c takes right-hand side c alone: it waits for x_{b+1}, subtracts the
-// fold and L_{b+1,b}^T x_{b+1} (the tile staged in LDS at the start),
-// substitutes, writes B and publishes its column.
+// the four waves fold the blocks j >= b + 3 as their payloads arrive, then
+// wave c takes right-hand side c alone: it subtracts the fold, waits for
+// x_{b+2} and subtracts L_{b+2,b}^T x_{b+2}, waits for x_{b+1} and subtracts
+// L_{b+1,b}^T x_{b+1}, substitutes, writes B and publishes its column.
 // Fold layout: thread (r, p) covers output row r of the block (column r of
 // each L_jb) and rows 16 p .. 16 p + 15 of every folded block; consecutive
 // r are consecutive addresses, so each wave reads 64 contiguous doubles per
 // row.  Each quarter p accumulates in block order; the quarters are then
-// combined in order p = 0..3.  Then y_b minus it; minus L_{b+1,b}^T x_{b+1}
-// as four partial sums (rows k = 4 i + r, ascending) added as
-// (d0 + d1) + (d2 + d3); then the substitution (sv_chains_bwd).
+// combined in order p = 0..3.  Then y_b minus it; minus the two products,
+// each as four partial sums (rows k = 4 i + r, ascending) added as
+// (d0 + d1) + (d2 + d3); then the substitution (sv_chain64_bwd).
 // The workgroup with ticket g of the backward sweep (passes interleaved in
 // ticket order, as in the forward sweep).
-template <int RC>
+template <int RC, bool WIDE>
 __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, int64_t lda, int64_t n,
                                                 double* __restrict__ B, int64_t nc, int64_t ldb,
                                                 const double* __restrict__ Ypay, double* Xpay, SvWs* ws,
                                                 int64_t wait_ticks, int32_t npass, int64_t pstride, int32_t g) {
   static_assert(RC >= 1 && RC <= SV_THREADS / 64, "one chain wave per right-hand side");
   __shared__ double part[4][SV_NB][RC + 1];
-  __shared__ double Lbb[SV_NB][SV_NB + 1];
-  __shared__ double Lsub[SV_NB][SV_NB + 1];  // L_{b+1,b}
-  __shared__ double xlds[RC][SV_NB];         // x_{b+1}, broadcast to the chain wave's lanes
+  __shared__ alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block, L_{b+1,b} and L_{b+2,b}, transposed:
+  __shared__ alignas(16) double Ls1[SV_NB][SV_TS];  // rows of lanes
+  __shared__ alignas(16) double Ls2[WIDE ? SV_NB : 1][SV_TS];  // (in registers, later, when not WIDE)
   __shared__ double rdiag[SV_NB];
   const int tid = threadIdx.x;
   const int32_t nb = (int32_t)((n + SV_NB - 1) / SV_NB);
@@ -433,15 +715,23 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
   // the chain wave's own entries of y (published by the forward sweep, an
   // earlier launch)
   const double yown = w < nc ? Ypay[((int64_t)b * SV_NB + lane) * RC + w] : 0.0;
-  sv_stage_diag(L, lda, r0, nr, Lbb, rdiag);
   {
-    const int64_t j0 = r0 + SV_NB;
-    for (int e = tid; e < SV_NB * SV_NB; e += SV_THREADS) {
-      const int k = e / SV_NB, i = e % SV_NB;
-      Lsub[k][i] = (b + 1 < nb && j0 + k < n && i < nr) ? L[(j0 + k) * lda + r0 + i] : 0.0;
+    const int64_t j1 = r0 + SV_NB, j2 = r0 + 2 * SV_NB;
+    double td[16], t1[16], t2[16];
+    sv_tile_load(L, lda, n, r0, r0, td);
+    if (b + 1 < nb) sv_tile_load(L, lda, n, j1, r0, t1);
+    if (WIDE && b + 2 < nb) sv_tile_load(L, lda, n, j2, r0, t2);
+    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[k][i] = v; });
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int k = p + 4 * e;
+      if (b + 1 < nb) Ls1[r][k] = j1 + k < n ? t1[e] : 0.0;
+      if constexpr (WIDE) {
+        if (b + 2 < nb) Ls2[r][k] = j2 + k < n ? t2[e] : 0.0;
+      }
     }
   }
-  // Only the blocks b <= nb - 3 fold, and they are full, so the column
+  // Only the blocks b <= nb - 4 fold, and they are full, so the column
   // r0 + r is inside the matrix.  A full block j is read with 16 plain
   // loads in flight together; the ragged last one clamps rows past n to
   // its last row (in bounds) and selects them away (a wave-uniform choice
@@ -468,11 +758,11 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
   // row 16 p + (l & 15), column (l >> 4) % RC (lanes past 16 RC repeat)
   const int xrow = lane & 15, xcol = (lane >> 4) % RC;
   auto xload = [&](int32_t j) { return sv_pay_ld(Xpay + ((int64_t)j * SV_NB + 16 * p + xrow) * RC + xcol); };
-  const int32_t jlast = b + 2;  // blocks nb - 1 down to b + 2
+  const int32_t jlast = b + 3;  // blocks nb - 1 down to b + 3
   double acc[RC];
 #pragma unroll
   for (int c = 0; c < RC; ++c) acc[c] = 0.0;
-  // the last folded tile (block b + 2) is read before any wait
+  // the last folded tile (block b + 3) is read before any wait
   double lt[16], lc[16], xa = 0.0;
   bool ok = true;
   if (jlast < nb) {
@@ -518,30 +808,36 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
     const int c = w;
     const double sm = ((part[0][lane][c] + part[1][lane][c]) + part[2][lane][c]) + part[3][lane][c];
     double v = lane < nr ? yown - sm : 0.0;
-    // column `lane` of L_{b+1,b} into registers before the wait
-    double lcol[SV_NB];
-#pragma unroll
-    for (int k = 0; k < SV_NB; ++k) lcol[k] = Lsub[k][lane];
-#pragma unroll
-    for (int k = 0; k < SV_NB; ++k) asm volatile("" : "+v"(lcol[k]));  // in registers before the wait
+    double x[4], l1[SV_NB], lc2[SV_NB];
+    const double rl = rdiag[lane];
     bool got = all_ok;
-    if (got && b + 1 < nb) {
-      // x_{b+1}, column c: lane k holds entry k
-      double xp = sv_pay_ld(Xpay + ((int64_t)(b + 1) * SV_NB + lane) * RC + c);
-      got = sv_wave_wait_full([&] { xp = sv_pay_ld(Xpay + ((int64_t)(b + 1) * SV_NB + lane) * RC + c); },
-                              [&] { return sv_pending(xp); }, ws, wait_ticks);
-      if (got) {
-        // L_{b+1,b}^T x_{b+1}: x_{b+1} through LDS, four partial sums over
-        // k = 4 i + r, then (d0 + d1) + (d2 + d3)
-        xlds[c][lane] = xp;
-        double d[4] = {0.0, 0.0, 0.0, 0.0};
+    if (got && b + 2 < nb) {
+      if constexpr (WIDE) {
+        sv_coefs(Ls2, lane, l1);
+      } else {  // column `lane` of L_{b+2,b} from memory (rows past n: their x is zero)
+        const int64_t j2 = r0 + 2 * SV_NB;
 #pragma unroll
-        for (int k = 0; k < SV_NB; ++k) d[k & 3] = __builtin_fma(lcol[k], xlds[c][k], d[k & 3]);
-        v = v - ((d[0] + d[1]) + (d[2] + d[3]));
+        for (int k = 0; k < SV_NB; ++k) l1[k] = L[(j2 + k < n ? j2 + k : n - 1) * lda + r0 + lane];
       }
+      sv_pin(l1);
+      got = sv_wait_col<RC, WIDE, false>(Xpay + (int64_t)(b + 2) * SV_NB * RC + c, x, lane, ws, wait_ticks);
+      if (got) v = v - sv_dot64(l1, x);
     }
+    // column `lane` of L_{b+1,b} (and, WIDE, of L_bb scaled by the reciprocal
+    // of its pivot) into registers before the wait for the neighbour
+    if constexpr (WIDE) {
+      sv_coefs(Lbb, lane, rl, lc2);
+      sv_pin(lc2);
+    }
+    if (got && b + 1 < nb) {
+      sv_coefs(Ls1, lane, l1);
+      sv_pin(l1);
+      got = sv_wait_col<RC, WIDE, true>(Xpay + (int64_t)(b + 1) * SV_NB * RC + c, x, lane, ws, wait_ticks);
+      if (got) v = v - sv_dot64(l1, x);
+    }
+    if constexpr (!WIDE) sv_coefs(Lbb, lane, rl, lc2);
     if (lane >= nr) v = 0.0;
-    sv_chains_bwd<1>(&v, Lbb, rdiag, lane);
+    v = sv_chain64_bwd(v * rl, lc2);
     if (lane < nr) B[(r0 + lane) * ldb + c] = v;
     if (got) sv_pay_st(Xpay + ((int64_t)b * SV_NB + lane) * RC + c, lane < nr ? v : 0.0);
     __builtin_amdgcn_s_setprio(0);
@@ -549,26 +845,26 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
 }
 
 // One solve per launch pair: the ticket from the solve's own counters.
-template <int RC>
-__global__ __launch_bounds__(SV_THREADS, 2) void sv_forward(const double* __restrict__ L, int64_t lda, int64_t n,
+template <int RC, bool WIDE>
+__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_forward(const double* __restrict__ L, int64_t lda, int64_t n,
                                                          const double* __restrict__ B, int64_t nc, int64_t ldb,
                                                          double* Ypay, double* __restrict__ Xpay, SvWs* ws,
                                                          int64_t wait_ticks, int32_t npass, int64_t pstride) {
   __shared__ int32_t s_g;
   if (threadIdx.x == 0) s_g = __hip_atomic_fetch_add(&ws->ticket_f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  sv_forward_run<RC>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
+  sv_forward_run<RC, WIDE>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
 }
 
-template <int RC>
-__global__ __launch_bounds__(SV_THREADS, 2) void sv_backward(const double* __restrict__ L, int64_t lda, int64_t n,
+template <int RC, bool WIDE>
+__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_backward(const double* __restrict__ L, int64_t lda, int64_t n,
                                                           double* __restrict__ B, int64_t nc, int64_t ldb,
                                                           const double* __restrict__ Ypay, double* Xpay, SvWs* ws,
                                                           int64_t wait_ticks, int32_t npass, int64_t pstride) {
   __shared__ int32_t s_g;
   if (threadIdx.x == 0) s_g = __hip_atomic_fetch_add(&ws->ticket_b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  sv_backward_run<RC>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
+  sv_backward_run<RC, WIDE>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
 }
 
 // ------------------------------------------------- several solves per launch
@@ -601,7 +897,8 @@ __device__ __forceinline__ void sv_take_job(const TcSolveJob* jobs, int64_t coun
   g = sv_uniform((int32_t)(t - jobs[job].first));
 }
 
-__global__ __launch_bounds__(SV_THREADS, 2) void sv_forward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
+template <bool WIDE>
+__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_forward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
                                                               int64_t wait_ticks) {
   int32_t j, g;
   sv_take_job(jobs, count, ctr, j, g);
@@ -613,11 +910,12 @@ __global__ __launch_bounds__(SV_THREADS, 2) void sv_forward_many(const TcSolveJo
   SvWs* ws = (SvWs*)work;
   double* ypay = (double*)(work + sv_jr256(sizeof(SvWs)));
   double* xpay = (double*)((char*)ypay + sv_jr256(8 * stride * np));
-  sv_forward_run<SV_RC_MID>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
+  sv_forward_run<SV_RC_MID, WIDE>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
                             (int32_t)np, stride, g);
 }
 
-__global__ __launch_bounds__(SV_THREADS, 2) void sv_backward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
+template <bool WIDE>
+__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_backward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
                                                                int64_t wait_ticks) {
   int32_t j, g;
   sv_take_job(jobs, count, ctr + 1, j, g);
@@ -627,7 +925,7 @@ __global__ __launch_bounds__(SV_THREADS, 2) void sv_backward_many(const TcSolveJ
   SvWs* ws = (SvWs*)work;
   const double* ypay = (const double*)(work + sv_jr256(sizeof(SvWs)));
   double* xpay = (double*)((char*)ypay + sv_jr256(8 * stride * np));
-  sv_backward_run<SV_RC_MID>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
+  sv_backward_run<SV_RC_MID, WIDE>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
                              (int32_t)np, stride, g);
 }
 
@@ -689,7 +987,11 @@ __global__ __launch_bounds__(SV_THREADS) void sv_invert_diag(const double* __res
   const int32_t b = blockIdx.x;
   const int64_t r0 = (int64_t)b * SV_NB;
   const int nr = n - r0 < SV_NB ? (int)(n - r0) : SV_NB;
-  sv_stage_diag(L, lda, r0, nr, Lbb, rdiag);
+  {
+    double td[16];
+    sv_tile_load(L, lda, n, r0, r0, td);
+    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[i][k] = v; });
+  }
   __syncthreads();
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double* D = Dinv + (int64_t)b * SV_NB * SV_NB;
@@ -1162,12 +1464,21 @@ SvMap sv_map(void* work, int64_t n, int64_t pw, int64_t npass = 1) {
   m.xpay = (double*)((char*)m.ypay + sv_r256(8 * m.entries));
   return m;
 }
-void sv_launch_fill(const SvMap& m, hipStream_t st) {
+void sv_launch_fill(const SvMap& m, hipStream_t st, int words = SV_COUNTER_WORDS) {
   int64_t blocks = (m.entries + 255) / 256;
   blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
-  hipLaunchKernelGGL(sv_fill, dim3((unsigned)blocks), dim3(256), 0, st, m.ws, SV_COUNTER_WORDS, m.ypay, m.entries);
+  hipLaunchKernelGGL(sv_fill, dim3((unsigned)blocks), dim3(256), 0, st, m.ws, words, m.ypay, m.entries);
 }
 }  // namespace
+
+// Which form of the sweeps a launch of `blocks` workgroups takes: up to four
+// per CU the chain's latency sets the time, beyond that the folds' share of
+// the chip.  Measured, WIDE and not (us; before: 2.4 us a block step where
+// WIDE takes 1.6): n=1500, 1 column: 97, 96 (127 before); n=8192, 16 columns,
+// 512 workgroups: 771, 990 (950); n=16384, 16 columns, 1024: 2160, 2205
+// (2155); n=32768, 8 columns, 1024: 4420, 4620 (4580); n=8192, 64 columns,
+// 2048: 1780, 1495 (1460); n=32768, 64 columns, 8192: 25100, 17650 (17500).
+static bool sv_wide(int64_t blocks) { return blocks <= 1024; }
 
 int64_t tc_solve_ws_bytes(int64_t n, int64_t nrhs, bool inv) {
   return sv_r256(sizeof(SvWs)) + 2 * sv_r256(8 * sv_pay_entries(n, sv_pay_width(nrhs, inv)) * sv_npass(nrhs, inv));
@@ -1230,8 +1541,11 @@ int tc_launch_solve_many(const TcSolveJob* jobs, int64_t count, int64_t tickets,
   bx = bx < 1 ? 1 : (bx > 64 ? 64 : bx);
   const int64_t by = count < 65535 ? count : 65535;
   hipLaunchKernelGGL(sv_fill_many, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, st, jobs, count, ctr);
-  hipLaunchKernelGGL(sv_forward_many, dim3((unsigned)tickets), dim3(SV_THREADS), 0, st, jobs, count, ctr, wait_ticks);
-  hipLaunchKernelGGL(sv_backward_many, dim3((unsigned)tickets), dim3(SV_THREADS), 0, st, jobs, count, ctr, wait_ticks);
+  const bool wide = sv_wide(tickets);
+  hipLaunchKernelGGL(wide ? sv_forward_many<true> : sv_forward_many<false>, dim3((unsigned)tickets), dim3(SV_THREADS),
+                     0, st, jobs, count, ctr, wait_ticks);
+  hipLaunchKernelGGL(wide ? sv_backward_many<true> : sv_backward_many<false>, dim3((unsigned)tickets),
+                     dim3(SV_THREADS), 0, st, jobs, count, ctr, wait_ticks);
   return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;
 }
 
@@ -1242,10 +1556,11 @@ int tc_launch_solve(const double* L, int64_t n, int64_t lda, int64_t T, double* 
   SvWs* ws = (SvWs*)work;
   if (nrhs <= SV_RC_SMALL) {  // measured faster for one or two right-hand sides
     const SvMap m = sv_map(work, n, SV_RC_SMALL);
-    sv_launch_fill(m, st);
-    hipLaunchKernelGGL(sv_forward<SV_RC_SMALL>, dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n,
+    sv_launch_fill(m, st, sizeof(SvWs) / 4);  // the status too
+    const bool wide = sv_wide(nb);
+    hipLaunchKernelGGL((wide ? sv_forward<SV_RC_SMALL, true> : sv_forward<SV_RC_SMALL, false>), dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n,
                        (const double*)B, nrhs, ldb, m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
-    hipLaunchKernelGGL(sv_backward<SV_RC_SMALL>, dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n, B, nrhs,
+    hipLaunchKernelGGL((wide ? sv_backward<SV_RC_SMALL, true> : sv_backward<SV_RC_SMALL, false>), dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n, B, nrhs,
                        ldb, (const double*)m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
     return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;
   }
@@ -1258,10 +1573,12 @@ int tc_launch_solve(const double* L, int64_t n, int64_t lda, int64_t T, double* 
   for (int64_t c0 = 0; c0 < nrhs; c0 += cols) {
     const int64_t nc = nrhs - c0 < cols ? nrhs - c0 : cols;
     const int64_t np = (nc + SV_RC_MID - 1) / SV_RC_MID;
-    sv_launch_fill(m, st);
-    hipLaunchKernelGGL(sv_forward<SV_RC_MID>, dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
+    // the first launch pair clears the call's status, later ones keep it
+    sv_launch_fill(m, st, c0 == 0 ? (int)(sizeof(SvWs) / 4) : SV_COUNTER_WORDS);
+    const bool wide = sv_wide(nb * np);
+    hipLaunchKernelGGL((wide ? sv_forward<SV_RC_MID, true> : sv_forward<SV_RC_MID, false>), dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
                        (const double*)(B + c0), nc, ldb, m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
-    hipLaunchKernelGGL(sv_backward<SV_RC_MID>, dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
+    hipLaunchKernelGGL((wide ? sv_backward<SV_RC_MID, true> : sv_backward<SV_RC_MID, false>), dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
                        B + c0, nc, ldb, (const double*)m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
   }
   return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;

@@ -79,3 +79,26 @@ def test_ragged_tiles(tc, T, n):
         print(f"T={T} n={n} {sched}: e_row {e:.2e}")
         assert e <= 1e-10
         assert np.array_equal(np.triu(L, 1), np.triu(A, 1))
+
+
+def test_solve_forms_agree(tc):
+    """A launch of more than 1024 block steps takes the sweeps' two-workgroup
+    form; a column's result is the same bits as alone (the wide form), and its
+    backward error meets the bar of the parity tests."""
+    import torch
+    n, nrhs = 4200, 64  # 66 blocks x 16 passes
+    A = inputs.se_kernel_device(n, 3)
+    L = A.clone()
+    assert tc.chol_factor(L, 128, "fork_join") == 0
+    B = torch.randn(n, nrhs, generator=torch.Generator(device="cuda").manual_seed(5), dtype=torch.float64,
+                    device="cuda")
+    X = B.clone()
+    tc.chol_solve(L, X, 128)
+    for c in (0, 3, 37, 63):
+        x = B[:, c:c + 1].contiguous()
+        tc.chol_solve(L, x, 128)
+        assert torch.equal(x[:, 0], X[:, c])
+    R = A @ X - B
+    eta = (R.abs().amax(0) / (A.abs().sum(1).max() * X.abs().amax(0) + B.abs().amax(0))).max().item()
+    print(f"eta {eta:.2e}")
+    assert eta <= 1e-12
