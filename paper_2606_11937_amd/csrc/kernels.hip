@@ -100,19 +100,21 @@ union alignas(512) TcSmem {
 };
 
 // POTRF(J, s): the diagonal block gid(J, s).
+template <bool SHARED>
 __device__ __forceinline__ void tc_run_potrf(double* A, int64_t lda, const TcGeom& g, int32_t J, int32_t s,
                                              TcWsHeader* h, TcPotrfSmem& sm) {
   const int64_t d0 = tc_row0(g, J, s);
-  const int bad = tc_potrf_tile(A + d0 * lda + d0, lda, tc_rows(g, J, s), sm);
+  const int bad = tc_potrf_tile<SHARED>(A + d0 * lda + d0, lda, tc_rows(g, J, s), sm);
   if (bad >= 0 && tc_tid() == 0) tc_report_fail(h, 1, d0 + bad + 1);
 }
 
 // TRSM(J, s, (I, a)): block (I, a) of sub-column gid(J, s).
+template <bool SHARED>
 __device__ __forceinline__ void tc_run_trsm(double* A, int64_t lda, const TcGeom& g, int32_t J, int32_t s, int32_t I,
                                             int32_t a, TcTrsmSmem& sm) {
   const int64_t r0 = tc_row0(g, I, a);
   const int64_t c0 = tc_row0(g, J, s);
-  tc_trsm_rows(A + r0 * lda + c0, A + c0 * lda + c0, lda, tc_rows(g, I, a), tc_rows(g, J, s), sm);
+  tc_trsm_rows<SHARED>(A + r0 * lda + c0, A + c0 * lda + c0, lda, tc_rows(g, I, a), tc_rows(g, J, s), sm);
 }
 
 // Rows [64 h, 64 h + 64) of the same unit (h = 0, 1), for launches that give
@@ -123,7 +125,7 @@ __device__ __forceinline__ void tc_run_trsm_half(double* A, int64_t lda, const T
   if (mr <= 0) return;
   const int64_t r0 = tc_row0(g, I, a) + 64 * h;
   const int64_t c0 = tc_row0(g, J, s);
-  tc_trsm_rows(A + r0 * lda + c0, A + c0 * lda + c0, lda, mr < 64 ? mr : 64, tc_rows(g, J, s), sm);
+  tc_trsm_rows<false>(A + r0 * lda + c0, A + c0 * lda + c0, lda, mr < 64 ? mr : 64, tc_rows(g, J, s), sm);
 }
 
 // Whether a product unit is a full diagonal block that tc_syrk_block takes.
@@ -131,13 +133,14 @@ __device__ __forceinline__ bool tc_syrk_fits(bool diag, int mr, int kd) {
   return diag && mr == 128 && kd > 0 && (kd & 15) == 0;
 }
 
-// C -= PA PB^T for a product unit, whichever body takes it.
+// C -= PA PB^T for a product unit of a persistent schedule, whichever body
+// takes it.
 __device__ __forceinline__ void tc_product_block(double* C, const double* PA, const double* PB, int64_t lda, int mr,
                                                  int mc, int kd, bool diag, TcSmem& sm) {
   if (tc_syrk_fits(diag, mr, kd))
-    (void)tc_syrk_block<false>(C, PA, lda, kd, sm.upd, sm.potrf);
+    (void)tc_syrk_block<false, true>(C, PA, lda, kd, sm.upd, sm.potrf);
   else
-    tc_update_block(C, PA, PB, lda, mr, mc, kd, diag, sm.upd);
+    tc_update_block<true>(C, PA, PB, lda, mr, mc, kd, diag, sm.upd);
 }
 
 // UPDATE(J, (I, a), (K, b)): K-depth the whole tile column J.
@@ -180,7 +183,7 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_potrf(double* A, int64_t 
                                                           TcWs ws) {
   __shared__ TcPotrfSmem sm;
   if (tc_err_set(ws.hdr) || ws.noop) return;
-  tc_run_potrf(A, lda, g, J, s, ws.hdr, sm);
+  tc_run_potrf<false>(A, lda, g, J, s, ws.hdr, sm);
 }
 
 // The panel-update and trailing-update launches each carry the next POTRF:
@@ -206,11 +209,11 @@ __device__ __forceinline__ void tc_run_update_potrf(double* A, int64_t lda, cons
   const double* P = A + d0 * lda + c0;
   int bad;
   if (tc_syrk_fits(true, td, kd)) {
-    bad = tc_syrk_block<true>(D, P, lda, kd, sm.upd, sm.potrf);
+    bad = tc_syrk_block<true, false>(D, P, lda, kd, sm.upd, sm.potrf);
   } else {
     tc_update_block(D, P, P, lda, td, td, kd, true, sm.upd);
     __syncthreads();
-    bad = tc_potrf_tile(D, lda, td, sm.potrf);
+    bad = tc_potrf_tile<false>(D, lda, td, sm.potrf);
   }
   if (bad >= 0 && tc_tid() == 0) tc_report_fail(h, 1, d0 + bad + 1);
 }
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(TC_THREADS, 2) void tc_fj_update_lp_range(double* A
   tc_run_update_lp<PREC>(A, lda, g, J, tc_decode_trailing(g, J, J, first + blockIdx.x), P, ldp, sm.upd);
   if (first == 0 && blockIdx.x == 0) {
     __syncthreads();
-    tc_run_potrf(A, lda, g, J + 1, 0, ws.hdr, sm.potrf);
+    tc_run_potrf<false>(A, lda, g, J + 1, 0, ws.hdr, sm.potrf);
   }
 }
 
@@ -462,15 +465,19 @@ __device__ __forceinline__ void tc_unit_publish(const TcGeom& g, const TcWs& ws,
   });
 }
 
-// End of a unit: every wave's stores have reached the L2, and every thread is
-// done with the unit's LDS.  The device-wide release (the write-back of the
-// XCD's L2, which holds up every workgroup on it) is thread 0's alone, in
-// front of its publish: one per unit where a fence in every wave made four.
-// Measured, 4096 matrices of orders 32 .. 2048 with a solve each: 65.3 ms of
-// kernel time with four, 39.9 ms with one; one matrix, n = 8192, T = 512:
-// 11.5 and 10.9 ms.
+// End of a unit: every wave's stores are complete at device scope, and every
+// thread is done with the unit's LDS.  The units of these schedules store
+// their results with device-scope stores (tc_st<true>), which are complete
+// when the wave's memory counter says so; what is left of a release is that
+// the publish follows them.  (With ordinary stores each publish needs the
+// XCD's whole L2 written back, which takes about 1.2 us and holds up every
+// workgroup of the XCD: at some 250,000 units that, not the units, was the
+// time of the batched launch.)
+// Measured, kernel time, 4096 matrices of orders 32 .. 2048 with a solve
+// each: 38.4 -> 34.5 ms.
 __device__ __forceinline__ void tc_unit_stored() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
 }
 
@@ -532,10 +539,7 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     if (threadIdx.x == 0) {
       const TcGeom cg = s_ctx.g;
       const TcUnit prev = s_unit;
-      if (prev.kind >= 0 && !tc_err_set(ws.hdr)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        tc_unit_publish(cg, ws, prev);
-      }
+      if (prev.kind >= 0 && !tc_err_set(ws.hdr)) tc_unit_publish(cg, ws, prev);
       const int64_t t = __hip_atomic_fetch_add(&ws.hdr->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       int32_t go = 0;
       if (t < s_ctx.total) {
@@ -568,9 +572,9 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     } else if (u.kind == TC_UNIT_UPDATE || u.kind == TC_UNIT_PANEL) {
       tc_run_product(A, lda, cg, u, sm);
     } else if (u.kind == TC_UNIT_TRSM) {
-      tc_run_trsm(A, lda, cg, u.J, u.K, u.I, u.a, sm.trsm);
+      tc_run_trsm<true>(A, lda, cg, u.J, u.K, u.I, u.a, sm.trsm);
     } else {
-      tc_run_potrf(A, lda, cg, u.J, u.a, ws.hdr, sm.potrf);
+      tc_run_potrf<true>(A, lda, cg, u.J, u.a, ws.hdr, sm.potrf);
     }
     tc_unit_stored();
   }
@@ -955,7 +959,7 @@ __device__ __forceinline__ void tc_round_strip(const double* __restrict__ A, int
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        if (rb + q < mr) P[(r0 + rb + q) * ldp + c0 + k] = tc_round_lp<TC_PREC_FP32>(v[q]);
+        if (rb + q < mr) tc_st<true>(P + (r0 + rb + q) * ldp + c0 + k, tc_round_lp<TC_PREC_FP32>(v[q]));
     }
 }
 
@@ -979,7 +983,6 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       if (s_unit.kind >= 0 && s_unit.kind != TC_UNIT_SOLVE && s_run) {
         const TcWs pws = tc_global_ws(s_mat.ws);
         if (!tc_err_set(pws.hdr)) {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
           tc_unit_publish(s_mat.g, pws, s_unit);
           __hip_atomic_fetch_add(tc_global(s_mat.done), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1024,19 +1027,19 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const float* P = tc_global(s_mat.P);
         const int64_t ldp = tc_ctx64(s_mat.ldp);
         const int64_t ri = tc_row0(cg, u.I, u.a), rk = tc_row0(cg, u.K, u.b), cj = (int64_t)u.J * cg.T;
-        tc_update_block_lp<TC_PREC_FP32>(A + ri * lda + rk, P + ri * ldp + cj, P + rk * ldp + cj, lda, ldp,
+        tc_update_block_lp<TC_PREC_FP32, true>(A + ri * lda + rk, P + ri * ldp + cj, P + rk * ldp + cj, lda, ldp,
                                          tc_rows(cg, u.I, u.a), tc_rows(cg, u.K, u.b), (int)tc_tdim(cg, u.J),
                                          ri == rk, sm.f.upd);
       } else if (u.kind == TC_UNIT_UPDATE || u.kind == TC_UNIT_PANEL) {
         tc_run_product(A, lda, cg, u, sm.f);
       } else if (u.kind == TC_UNIT_TRSM) {
-        tc_run_trsm(A, lda, cg, u.J, u.K, u.I, u.a, sm.f.trsm);
+        tc_run_trsm<true>(A, lda, cg, u.J, u.K, u.I, u.a, sm.f.trsm);
         if (prec == TC_PREC_FP32 && u.K == tc_sb(cg, u.J) - 1 && u.I > u.J) {
           __syncthreads();  // the strip's new block is visible to the whole workgroup
           tc_round_strip(A, lda, cg, u.J, u.I, u.a, tc_global(s_mat.P), tc_ctx64(s_mat.ldp));
         }
       } else if (u.kind == TC_UNIT_POTRF) {
-        tc_run_potrf(A, lda, cg, u.J, u.a, tc_global(s_mat.ws.hdr), sm.f.potrf);
+        tc_run_potrf<true>(A, lda, cg, u.J, u.a, tc_global(s_mat.ws.hdr), sm.f.potrf);
       } else {
         tc_wg_solve_unit(A, lda, cg.n, tc_global(s_mat.b), tc_ctx64(s_mat.nrhs), tc_ctx64(s_mat.ldb),
                          tc_ctx32(s_mat.refine) != 0, tc_global(s_mat.A0), tc_ctx64(s_mat.lda0), tc_global(s_mat.b0),
@@ -1061,7 +1064,6 @@ __device__ __forceinline__ int32_t tc_grid_barrier(const TcWs& ws, int64_t targe
   tc_unit_stored();
   if (threadIdx.x == 0) {
     int32_t go = 1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __hip_atomic_fetch_add(&ws.hdr->bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t t0 = wall_clock64();
     while (__hip_atomic_load(&ws.hdr->bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
@@ -1089,13 +1091,13 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const int64_t cnt = link == 0 ? 1 : link == 1 ? tc_trsm_count(g, J, sc) : tc_panel_count(g, J, sc);
         for (int64_t i = blockIdx.x; i < cnt && !ws.noop; i += grid) {
           if (link == 0) {
-            tc_run_potrf(A, lda, g, J, sc, ws.hdr, sm.potrf);
+            tc_run_potrf<true>(A, lda, g, J, sc, ws.hdr, sm.potrf);
           } else if (link == 1) {
             const TcUnit u = tc_decode_trsm(g, J, sc, i);
-            tc_run_trsm(A, lda, g, J, sc, u.I, u.a, sm.trsm);
+            tc_run_trsm<true>(A, lda, g, J, sc, u.I, u.a, sm.trsm);
           } else {
             const TcUnit u = tc_decode_panel(g, J, sc, i);
-            tc_run_panel(A, lda, g, u, sm.upd);
+            tc_run_product(A, lda, g, u, sm);
           }
           __syncthreads();
         }
@@ -1108,7 +1110,7 @@ __global__ __launch_bounds__(TC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     const int64_t nu = tc_trailing_units(g, J);
     for (int64_t i = blockIdx.x; i < nu && !ws.noop; i += grid) {
       const TcUnit u = tc_decode_trailing(g, J, J, i);
-      tc_run_update(A, lda, g, u, sm.upd);
+      tc_run_product(A, lda, g, u, sm);
       __syncthreads();
     }
     if (nu > 0) {

@@ -61,6 +61,27 @@ __device__ __forceinline__ tc_v4d tc_mfma_neg(double a, double b, tc_v4d c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
 }
 
+// Stores of a unit's results.  SHARED: by the persistent schedules, whose
+// units are read by workgroups of the same launch on other XCDs: a
+// device-scope store goes through the XCD's L2 to memory, so a finished unit
+// needs no write-back of that L2 before it is published (see tc_unit_stored).
+template <bool SHARED, class V>
+__device__ __forceinline__ void tc_st(V* p, V v) {
+  if constexpr (SHARED)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+template <bool SHARED>
+__device__ __forceinline__ void tc_st2(double* p, double x, double y) {
+  if constexpr (SHARED) {
+    tc_st<true>(p, x);
+    tc_st<true>(p + 1, y);
+  } else {
+    *(tc_d2*)p = tc_d2{x, y};
+  }
+}
+
 // Four consecutive doubles of one row, as two 16-byte loads.
 struct tc_q4 {
   tc_d2 lo, hi;
@@ -112,6 +133,7 @@ typedef double tc_d2a16 __attribute__((ext_vector_type(2), aligned(16)));
 
 __device__ __forceinline__ int tc_swz(int r) { return r & 7; }
 
+template <bool SHARED = false>
 __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const double* __restrict__ PA,
                                                 const double* __restrict__ PB, int64_t lda, int mr, int mc,
                                                 int kd, bool diag, TcUpdSmem& sm) {
@@ -268,7 +290,7 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int c = wn * 64 + j * 16 + ocol;
-          if (!diag || r >= c) rp[16 * j] = v[4 * q + j] - acc[i][j][q];
+          if (!diag || r >= c) tc_st<SHARED>(rp + 16 * j, v[4 * q + j] - acc[i][j][q]);
         }
       }
     };
@@ -302,7 +324,8 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int c = wn * 64 + j * 16 + ocol;
-          if (r < mr && c < mc && (!diag || r >= c)) C[(int64_t)r * lda + c] = v[4 * q + j] - acc[i][j][q];
+          if (r < mr && c < mc && (!diag || r >= c))
+            tc_st<SHARED>(C + (int64_t)r * lda + c, v[4 * q + j] - acc[i][j][q]);
         }
       }
     };
@@ -626,18 +649,19 @@ __device__ __forceinline__ tc_v4d tc_strip_get(const double* __restrict__ X, int
   }
   return a;
 }
+template <bool SHARED>
 __device__ __forceinline__ void tc_strip_put(double* __restrict__ X, int64_t lda, int mr, int td, int j, int lane,
                                              tc_v4d a) {
   const int r16 = lane & 15, c = 16 * j + 4 * (lane >> 4);
   if (r16 >= mr) return;
   double* g = X + (int64_t)r16 * lda + c;
   if (td == 128) {
-    *(tc_d2*)g = tc_d2{a[0], a[1]};
-    *(tc_d2*)(g + 2) = tc_d2{a[2], a[3]};
+    tc_st2<SHARED>(g, a[0], a[1]);
+    tc_st2<SHARED>(g + 2, a[2], a[3]);
   } else {
 #pragma unroll
     for (int m = 0; m < 4; ++m)
-      if (c + m < td) g[m] = a[m];
+      if (c + m < td) tc_st<SHARED>(g + m, a[m]);
   }
 }
 
@@ -709,7 +733,7 @@ __host__ __device__ constexpr int tc_stage_end(int b) { return (b * (b + 1) / 2 
 
 // Step B of a strip.  FIRST: the workgroup's first strips, whose steps also
 // move block row B of L into LDS (all waves, one barrier).
-template <int B, bool FIRST>
+template <int B, bool FIRST, bool SHARED>
 __device__ __forceinline__ void tc_trsm_step(double* __restrict__ X, int64_t lda, int mr, int td, int nbk, int lane,
                                              tc_v4d (&x)[8], const TcTrsmStage& st, TcTrsmSmem& sm) {
   const int s4 = lane >> 4;
@@ -742,14 +766,15 @@ __device__ __forceinline__ void tc_trsm_step(double* __restrict__ X, int64_t lda
   }
   tc_subst16(y, o);
   x[B] = y[0];
-  tc_strip_put(X, lda, mr, td, B, lane, tc_transpose4(y[0]));
+  tc_strip_put<SHARED>(X, lda, mr, td, B, lane, tc_transpose4(y[0]));
   if constexpr (B + 1 < 8) {
-    if (B + 1 < nbk) tc_trsm_step<B + 1, FIRST>(X, lda, mr, td, nbk, lane, x, st, sm);
+    if (B + 1 < nbk) tc_trsm_step<B + 1, FIRST, SHARED>(X, lda, mr, td, nbk, lane, x, st, sm);
   }
 }
 
 // A TRSM unit, or the mr <= 64 rows of half a unit as a workgroup of its own
 // (each row's arithmetic is the same): wave w takes the strips w and w + 4.
+template <bool SHARED>
 __device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const double* __restrict__ L, int64_t lda,
                                              int mr_in, int td_in, TcTrsmSmem& sm) {
   const int mr = tc_uniform((int32_t)mr_in), td = tc_uniform((int32_t)td_in);
@@ -769,13 +794,13 @@ __device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const doubl
     for (int k = b > 0 ? tc_stage_end(b - 1) : 0; k < tc_stage_end(b); ++k) tc_stage_load(L, lda, td, k, st);
     __builtin_amdgcn_sched_barrier(0);
   }
-  tc_trsm_step<0, true>(X0, lda, rows(16 * w), td, nbk, lane, x, st, sm);
+  tc_trsm_step<0, true, SHARED>(X0, lda, rows(16 * w), td, nbk, lane, x, st, sm);
   if (16 * w + 64 < mr) {
     asm volatile("" ::: "memory");  // operands are read from LDS again, not kept in registers
     double* X1 = X0 + 64 * lda;
 #pragma unroll
     for (int b = 0; b < 8; ++b) x[b] = tc_strip_get(X1, lda, rows(16 * w + 64), td, b, lane);
-    tc_trsm_step<0, false>(X1, lda, rows(16 * w + 64), td, nbk, lane, x, st, sm);
+    tc_trsm_step<0, false, SHARED>(X1, lda, rows(16 * w + 64), td, nbk, lane, x, st, sm);
   }
 }
 
@@ -895,6 +920,7 @@ __device__ __forceinline__ void tc_pk_load(const double* __restrict__ D, int64_t
 }
 
 // Block column c of the factor back to D, halves wv, wv + nw, ...
+template <bool SHARED>
 __device__ __forceinline__ void tc_pk_store_col(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm, int c,
                                                 int nbk, int wv, int nw, int lane) {
   const int r8 = lane >> 3, c2 = 2 * (lane & 7);
@@ -905,10 +931,10 @@ __device__ __forceinline__ void tc_pk_store_col(double* __restrict__ D, int64_t 
     double* g = D + (int64_t)R * lda + C;
     const tc_d2a16 x = *(const tc_d2a16*)tc_half_at(sm, tc_pk(i, c), h & 1, lane);
     if (td == 128 && i != c) {
-      *(tc_d2*)g = tc_d2{x.x, x.y};
+      tc_st2<SHARED>(g, x.x, x.y);
     } else if (R < td) {
-      if (C <= R) g[0] = x.x;
-      if (C + 1 <= R) g[1] = x.y;
+      if (C <= R) tc_st<SHARED>(g, x.x);
+      if (C + 1 <= R) tc_st<SHARED>(g + 1, x.y);
     }
   }
 }
@@ -992,7 +1018,7 @@ __device__ __forceinline__ void tc_pk_diag(TcPotrfSmem& sm, int b, int nb, int c
 
 // LOAD: the tile is read from D; otherwise it is in sm.blk already (complete
 // for every thread).
-template <bool LOAD>
+template <bool LOAD, bool SHARED>
 __device__ __forceinline__ int tc_potrf_body(double* __restrict__ D, int64_t lda, int td_in, TcPotrfSmem& sm) {
   const int td = tc_uniform((int32_t)td_in);
   const int tid = tc_tid(), lane = tid & 63, w = tid >> 6;
@@ -1081,18 +1107,19 @@ __device__ __forceinline__ int tc_potrf_body(double* __restrict__ D, int64_t lda
       }
       // block column b - 2, final since step b - 2, goes back to D here,
       // where these waves wait for wave 0 anyway
-      if (b >= 2) tc_pk_store_col(D, lda, td, sm, b - 2, nbk, wu - 1, 3, lane);
+      if (b >= 2) tc_pk_store_col<SHARED>(D, lda, td, sm, b - 2, nbk, wu - 1, 3, lane);
     }
     __syncthreads();
     fail = tc_uniform((int32_t)sm.fail);
   }
   if (fail >= 0) return fail;  // (the tile is left partly factored)
-  for (int c = nbk > 3 ? nbk - 3 : 0; c < nbk; ++c) tc_pk_store_col(D, lda, td, sm, c, nbk, wu, 4, lane);
+  for (int c = nbk > 3 ? nbk - 3 : 0; c < nbk; ++c) tc_pk_store_col<SHARED>(D, lda, td, sm, c, nbk, wu, 4, lane);
   return -1;
 }
 
+template <bool SHARED>
 __device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda, int td, TcPotrfSmem& sm) {
-  return tc_potrf_body<true>(D, lda, td, sm);
+  return tc_potrf_body<true, SHARED>(D, lda, td, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -1112,7 +1139,7 @@ __device__ __forceinline__ int tc_potrf_tile(double* __restrict__ D, int64_t lda
 // Alone on a CU, kd = 128: 13.1 us (20.2 us as a general update; 18400 cycles
 // of MFMAs, 7.7 us); with the POTRF 32.0 us (20.2 + 22.2 us as two bodies).
 // ---------------------------------------------------------------------------
-template <bool POTRF>
+template <bool POTRF, bool SHARED>
 __device__ __forceinline__ int tc_syrk_block(double* __restrict__ C, const double* __restrict__ P, int64_t lda, int kd,
                                              TcUpdSmem& sm, TcPotrfSmem& pm) {
   const int tid = tc_tid(), lane = tid & 63;
@@ -1204,13 +1231,13 @@ __device__ __forceinline__ int tc_syrk_block(double* __restrict__ C, const doubl
     for (int j = 0; j < 4; ++j)
       if (j <= wu) tc_acc_put(pm.blk[tc_pk(wu, j)], lane, 16, cd[j] - acd[j]);
     __syncthreads();
-    return tc_potrf_body<false>(C, lda, 128, pm);
+    return tc_potrf_body<false, SHARED>(C, lda, 128, pm);
   } else {
     auto cstore = [&](int i, int j, tc_v4d v) {
       double* p = C + (int64_t)(16 * i + s4) * lda + 16 * j + r16;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (i > j || 4 * q + s4 >= r16) p[(int64_t)(4 * q) * lda] = v[q];
+        if (i > j || 4 * q + s4 >= r16) tc_st<SHARED>(p + (int64_t)(4 * q) * lda, v[q]);
     };
 #pragma unroll
     for (int j = 0; j < 8; ++j)

@@ -105,7 +105,7 @@ __device__ __forceinline__ tc_v4f tc_mfma_lp<TC_PREC_BF16>(const tc_u4& a, const
 // Same contract as tc_update_block with PA, PB low-precision rows of leading
 // dimension ldp (elements); mr, mc <= 128.  The shared memory is the FP64
 // kernel's (the same 128 x 128-byte stage layout).
-template <int PREC>
+template <int PREC, bool SHARED = false>
 __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const typename TcLp<PREC>::elem* __restrict__ PA,
                                                    const typename TcLp<PREC>::elem* __restrict__ PB, int64_t lda,
                                                    int64_t ldp, int mr, int mc, int kd, bool diag, TcUpdSmem& sm) {
@@ -241,7 +241,7 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int c = wn * 64 + j * 16 + ocol;
-          if (!diag || r >= c) rp[16 * j] = v[4 * q + j] - (double)acc[i][j][q];
+          if (!diag || r >= c) tc_st<SHARED>(rp + 16 * j, v[4 * q + j] - (double)acc[i][j][q]);
         }
       }
     };
@@ -275,7 +275,7 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
         for (int j = 0; j < 4; ++j) {
           const int c = wn * 64 + j * 16 + ocol;
           if (r < mr && c < mc && (!diag || r >= c))
-            C[(int64_t)r * lda + c] = v[4 * q + j] - (double)acc[i][j][q];
+            tc_st<SHARED>(C + (int64_t)r * lda + c, v[4 * q + j] - (double)acc[i][j][q]);
         }
       }
     };
