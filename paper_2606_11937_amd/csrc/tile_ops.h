@@ -114,6 +114,12 @@ __device__ __forceinline__ double tc_el(const tc_q4& q, int m) {
 // buffer resource spans exactly the block's mr (mc) rows: rows beyond them
 // read as zero and are never stored.
 //
+// Rows of B are staged in the order of tc_pair_row, so that a lane's results
+// of column blocks j and j + 1 (j even) are neighbours in C, which is then
+// read and written 16 bytes a lane, 256 consecutive bytes of a row at a time.
+// Against 8 bytes a lane: a unit with K = 128 .. 384 in the batched launch
+// 46.5 -> 44.0 us, alone 24 -> 22.5 us; fork-join at order 32768 unchanged.
+//
 // Fragment registers roll half a chunk ahead: the high halves (k steps 2, 3)
 // of chunk c are read while the MFMAs of its low halves run; the barrier that
 // publishes chunk c+1 sits in the middle of chunk c; the low halves of chunk
@@ -133,6 +139,9 @@ typedef __attribute__((address_space(3))) void tc_lds_void;
 typedef double tc_d2a16 __attribute__((ext_vector_type(2), aligned(16)));
 
 __device__ __forceinline__ int tc_swz(int r) { return r & 7; }
+
+// The row of B (and column of C) that LDS row 16 i + r of its 64 holds.
+__device__ __forceinline__ int tc_pair_row(int i, int r) { return 32 * (i >> 1) + 2 * r + (i & 1); }
 
 template <bool SHARED = false>
 __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const double* __restrict__ PA,
@@ -157,9 +166,11 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
   const double* src = (const double*)tc_uniform((int64_t)(ws < 2 ? PA : PB));
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)src, (short)0, (int)((int64_t)nrow * tc_uniform(lda) * 8), 0x00020000);
-  const int rl0 = (w & 1) * 64 + (lane >> 3);
-  const unsigned vof0 = (unsigned)(rl0 * lda * 8 + 16 * ((lane & 7) ^ tc_swz(rl0)));
-  const unsigned rowstep = (unsigned)(8 * lda * 8);
+  const bool isb = ws >= 2;
+  const int rl0 = (w & 1) * 64 + (isb ? 2 : 1) * (lane >> 3);
+  const int kl0 = (lane & 7) ^ (lane >> 3);
+  const unsigned vof0 = (unsigned)(rl0 * lda * 8 + 16 * kl0);
+  auto rowof = [&](int q) { return isb ? tc_pair_row(q >> 1, 8 * (q & 1)) : 8 * q; };  // from rl0
   auto stage_load = [&](int st, int k0) {
 #pragma unroll
     for (int q = 0; q < 8; ++q)
@@ -167,7 +178,7 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
           rsrc,
           (tc_lds_void*)((char __attribute__((address_space(3)))*)(tc_lds_void*)&sm.tile[st][0][0] +
                          (ws * 8 + q) * 1024),
-          16, vof0 + q * rowstep, (unsigned)(k0 * 8), 0, 0);
+          16, vof0 + (unsigned)rowof(q) * (unsigned)(tc_uniform(lda) * 8), (unsigned)(k0 * 8), 0, 0);
   };
   // the ragged last chunk (kd % 16 != 0): ordinary guarded loads, zero past
   // kd or past the block's rows, stored where the direct loads would put them
@@ -175,9 +186,8 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
     const double* gb = w < 2 ? PA : PB;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int r = rl0 + q * 8;
-      const int j = (lane & 7) ^ tc_swz(r);
-      const int k = k0 + 2 * j;
+      const int r = rl0 + rowof(q);
+      const int k = k0 + 2 * kl0;
       const double* src = gb + (int64_t)(r < nrow ? r : 0) * lda + k;
       tc_d2 v;
       v.x = (r < nrow && k < kd) ? src[0] : 0.0;
@@ -264,34 +274,40 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
   if (!active) return;
 
   // epilogue: C -= acc on the stored part, one 16-row group at a time.  A
-  // full block reads its C values unconditionally (for a diagonal block the
-  // entries above the diagonal are read and left alone), the loads of the
-  // next group issued before the current one is stored, so each wave has at
-  // most one memory round trip outstanding per group instead of one per
-  // element; the scheduling barriers keep the compiler from hoisting more
-  // loads (each group takes 32 registers).  A ragged block reads from
-  // clamped positions and guards its stores.
-  const int orow = lane >> 4, ocol = lane & 15;
-  if (mr == 128 && mc == 128) {
-    double* cb = C + (int64_t)(wm * 64 + orow) * lda + wn * 64 + ocol;
-    double cv[2][16];
-    auto cload = [&](double(&v)[16], int i) {
+  // block of 128 columns reads its C values unconditionally (rows past mr
+  // read the last one; for a diagonal block the entries above the diagonal
+  // are read and left alone), the loads of the next group issued before the
+  // current one is stored, so each wave has at most one memory round trip
+  // outstanding per group instead of one per element; the scheduling barriers
+  // keep the compiler from hoisting more loads (each group takes 32
+  // registers).  Other blocks read from clamped positions too.
+  const int orow = lane >> 4, ocol = 2 * (lane & 15);
+  if (mc == 128) {
+    double* cb = C + wn * 64 + ocol;
+    tc_d2 cv[2][8];
+    auto cload = [&](tc_d2(&v)[8], int i) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const double* rp = cb + (int64_t)(i * 16 + 4 * q) * lda;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[4 * q + j] = rp[16 * j];
+        const int r = wm * 64 + i * 16 + 4 * q + orow;
+        const double* rp = cb + (int64_t)(r < mr ? r : mr - 1) * lda;
+        v[2 * q] = *(const tc_d2*)rp;
+        v[2 * q + 1] = *(const tc_d2*)(rp + 32);
       }
     };
-    auto cstore = [&](const double(&v)[16], int i) {
+    auto cstore = [&](const tc_d2(&v)[8], int i) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        double* rp = cb + (int64_t)(i * 16 + 4 * q) * lda;
         const int r = wm * 64 + i * 16 + 4 * q + orow;
+        double* rp = cb + (int64_t)r * lda;
+        if (r >= mr) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
-          if (!diag || r >= c) tc_st<SHARED>(rp + 16 * j, v[4 * q + j] - acc[i][j][q]);
+        for (int j = 0; j < 4; j += 2) {
+          const int c = wn * 64 + 16 * j + ocol;
+          const tc_d2 x = {v[2 * q + j / 2].x - acc[i][j][q], v[2 * q + j / 2].y - acc[i][j + 1][q]};
+          if (!diag || r > c)
+            tc_st2<SHARED>(rp + 16 * j, x.x, x.y);
+          else if (r == c)
+            tc_st<SHARED>(rp + 16 * j, x.x);
         }
       }
     };
@@ -313,7 +329,7 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
         const double* rp = C + (int64_t)(r < mr ? r : mr - 1) * lda;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
+          const int c = wn * 64 + 32 * (j >> 1) + ocol + (j & 1);
           v[4 * q + j] = rp[c < mc ? c : mc - 1];
         }
       }
@@ -324,7 +340,7 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
         const int r = wm * 64 + i * 16 + 4 * q + orow;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
+          const int c = wn * 64 + 32 * (j >> 1) + ocol + (j & 1);
           if (r < mr && c < mc && (!diag || r >= c))
             tc_st<SHARED>(C + (int64_t)r * lda + c, v[4 * q + j] - acc[i][j][q]);
         }
@@ -621,12 +637,14 @@ __device__ __forceinline__ void tc_swap_rows(double& a, double& b, bool wide) {
   b = __builtin_bit_cast(double, y);
 }
 // Between the substitution's layout (lane row g, item m: column 4 m + g) and
-// the strip's layout in memory (lane row g: columns 2 g, 2 g + 1, 2 g + 8 and
-// 2 g + 9), in which a 16-byte access of the wave covers 64 consecutive bytes
-// of every row.  (With four consecutive columns a lane, an access covered
-// every other 16 bytes, and device-scope stores of 8 bytes every fourth 8:
-// 512 of these units at a time took 70 us each in the batched launch, 45 us
-// this way; the launch of 4096 matrices with solves 34.5 -> 31.1 ms.)
+// the strip's in memory.  It is read with four consecutive columns a lane
+// (two adjacent 16-byte loads; pairs 8 columns apart, as below, were 7 %
+// slower a unit) and written with columns 2 g, 2 g + 1, 2 g + 8 and 2 g + 9
+// in lane row g, so that a 16-byte store of the wave covers 64 consecutive
+// bytes of every row.  (With four consecutive columns a lane there too and
+// device-scope stores of 8 bytes, each touched every fourth 8 bytes: 512 of
+// these units at a time took 70 us each in the batched launch, 42 us this
+// way; the launch of 4096 matrices with solves 34.5 -> 30.4 ms.)
 __device__ __forceinline__ tc_v4d tc_strip_out(tc_v4d v) {
   double a = v[0], b = v[1], c = v[2], d = v[3];
   tc_swap_rows(a, b, true);
@@ -637,30 +655,30 @@ __device__ __forceinline__ tc_v4d tc_strip_out(tc_v4d v) {
 }
 __device__ __forceinline__ tc_v4d tc_strip_in(tc_v4d v) {
   double a = v[0], b = v[1], c = v[2], d = v[3];
+  tc_swap_rows(a, c, true);
+  tc_swap_rows(b, d, true);
   tc_swap_rows(a, b, false);
   tc_swap_rows(c, d, false);
-  tc_swap_rows(a, b, true);
-  tc_swap_rows(c, d, true);
   return tc_v4d{a, b, c, d};
 }
 
-// Column block j of a strip (rows [0, mr) of X, mr <= 16) as stored: lane
-// (r, g) holds columns 16 j + 2 g, + 1, + 8 and + 9 of row r.  Rows past mr
-// and columns past td read clamped positions (selected to zero where they
-// matter).
+// Column block j of a strip (rows [0, mr) of X, mr <= 16) in those two forms:
+// lane (r, g) takes columns 16 j + 4 g .. + 3 of row r in, and gives 16 j +
+// 2 g, + 1, + 8 and + 9 out.  Rows past mr and columns past td read clamped
+// positions (selected to zero where they matter).
 __device__ __forceinline__ tc_v4d tc_strip_get(const double* __restrict__ X, int64_t lda, int mr, int td, int j,
                                                int lane) {
-  const int r16 = lane & 15, c = 16 * j + 2 * (lane >> 4);
+  const int r16 = lane & 15, c = 16 * j + 4 * (lane >> 4);
   const int rc = r16 < mr ? r16 : (mr > 0 ? mr - 1 : 0);
   const double* p = X + (int64_t)rc * lda;
   if (td == 128) {
-    const tc_d2 lo = *(const tc_d2*)(p + c), hi = *(const tc_d2*)(p + c + 8);
+    const tc_d2 lo = *(const tc_d2*)(p + c), hi = *(const tc_d2*)(p + c + 2);
     return tc_v4d{lo.x, lo.y, hi.x, hi.y};
   }
   tc_v4d a;
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
-    const int k = c + (m & 1) + 4 * (m & 2);
+    const int k = c + m;
     a[m] = p[k < td ? k : td - 1];
     a[m] = k < td ? a[m] : 0.0;
   }
