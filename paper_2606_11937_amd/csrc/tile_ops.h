@@ -140,6 +140,34 @@ typedef double tc_d2a16 __attribute__((ext_vector_type(2), aligned(16)));
 
 __device__ __forceinline__ int tc_swz(int r) { return r & 7; }
 
+// Rows [0, mr) of a block at p as a buffer: one 32-bit offset a lane, and
+// accesses past the last row read zero or are dropped.  SHARED as in tc_st.
+struct TcRows {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ TcRows(double* p, int64_t lda, int mr)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)tc_uniform((int64_t)p), (short)0,
+                                            (int)(tc_uniform((int32_t)mr) * tc_uniform(lda) * 8), 0x00020000)) {}
+  // at byte o + s of the block; s < 1024 and the same in all lanes
+  __device__ __forceinline__ tc_d2 ld2(unsigned o, unsigned s) const {
+    return __builtin_bit_cast(tc_d2, __builtin_amdgcn_raw_buffer_load_b128(r, o, s, 0));
+  }
+  // Stores without a branch: a lane whose `keep` is false stores nothing.  A
+  // 16-byte store takes its whole offset from the lane: with a scalar part
+  // the compiler leaves no wait state before the data registers are written
+  // again, and here the last lanes of a row then stored the new contents.
+  template <bool SHARED>
+  __device__ __forceinline__ void st2(bool keep, unsigned o, unsigned s, tc_d2 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, keep ? o + s : 0xFFFFF000u, 0,
+                                           SHARED ? 16 : 0);
+  }
+  template <bool SHARED>
+  __device__ __forceinline__ void st1(bool keep, unsigned o, unsigned s, double v) const {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, keep ? o : 0xFFFFF000u, s, SHARED ? 16 : 0);
+  }
+};
+
 // The row of B (and column of C) that LDS row 16 i + r of its 64 holds.
 __device__ __forceinline__ int tc_pair_row(int i, int r) { return 32 * (i >> 1) + 2 * r + (i & 1); }
 
@@ -231,92 +259,140 @@ __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const do
       Lb[i] = rd(0, 1, i, 0);
     }
   }
-  for (int c = 0; c < nch; ++c) {
+  auto high = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Ha[i] = rd(st, 0, i, 1);
+      Hb[i] = rd(st, 1, i, 1);
+    }
+  };
+  auto products = [&](const tc_d2(&fa)[4], const tc_d2(&fb)[4]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = tc_mfma(m ? fa[i].y : fa[i].x, m ? fb[j].y : fb[j].x, acc[i][j]);
+  };
+  for (int c = 0; c + 1 < nch; ++c) {
     const int st = c & 1;
+    if (active) {
+      high(st);
+      products(La, Lb);
+    }
+    // chunk c+1 has landed and this wave's reads of chunk c are complete;
+    // a plain barrier (a fenced one would also wait for unrelated traffic)
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    if (c + 2 < nch) stage(st, c + 2, nfull);  // chunk c's stage is free now
     if (active) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        Ha[i] = rd(st, 0, i, 1);
-        Hb[i] = rd(st, 1, i, 1);
+        La[i] = rd(st ^ 1, 0, i, 0);
+        Lb[i] = rd(st ^ 1, 1, i, 0);
       }
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = tc_mfma(m ? La[i].y : La[i].x, m ? Lb[j].y : Lb[j].x, acc[i][j]);
-    }
-    if (c + 1 < nch) {
-      // chunk c+1 has landed and this wave's reads of chunk c are complete;
-      // a plain barrier (a fenced one would also wait for unrelated traffic)
-      __builtin_amdgcn_s_waitcnt(0x0070);
-      __builtin_amdgcn_s_barrier();
-      if (c + 2 < nch) stage(st, c + 2, nfull);  // chunk c's stage is free now
-      if (active) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          La[i] = rd(st ^ 1, 0, i, 0);
-          Lb[i] = rd(st ^ 1, 1, i, 0);
-        }
-      }
-    }
-    if (active) {
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = tc_mfma(m ? Ha[i].y : Ha[i].x, m ? Hb[j].y : Hb[j].x, acc[i][j]);
+      products(Ha, Hb);
     }
   }
   if (!active) return;
 
-  // epilogue: C -= acc on the stored part, one 16-row group at a time.  A
-  // block of 128 columns reads its C values unconditionally (rows past mr
-  // read the last one; for a diagonal block the entries above the diagonal
-  // are read and left alone), the loads of the next group issued before the
-  // current one is stored, so each wave has at most one memory round trip
-  // outstanding per group instead of one per element; the scheduling barriers
-  // keep the compiler from hoisting more loads (each group takes 32
-  // registers).  Other blocks read from clamped positions too.
+  // the last chunk, and C -= acc on the stored part, in 16-row groups (32
+  // registers of C each).  A block of 128 columns reads its C values
+  // unconditionally (rows past mr read as zero and are not stored; for a
+  // diagonal block the entries above the diagonal are read and left alone):
+  // half of group 0 before the last half chunk's products, the rest and group
+  // 1 behind them, groups 2 and 3 as groups 0 and 1 are subtracted, and no
+  // store before the last load, as loads and stores of a wave complete in
+  // order: two memory round trips instead of five.  Measured: the batched
+  // launch of 4096 matrices 30.3 -> 29.7 ms, order 32768 187.8 -> 185.7 ms.
+  // (All of group 0 ahead takes registers that the persistent kernels spill.)
+  // Other blocks read from clamped positions, one group ahead of the stores.
   const int orow = lane >> 4, ocol = 2 * (lane & 15);
-  if (mc == 128) {
-    double* cb = C + wn * 64 + ocol;
-    tc_d2 cv[2][8];
-    auto cload = [&](tc_d2(&v)[8], int i) {
+  const bool pairs = mc == 128;
+  const TcRows cr(C, lda, mr);
+  const unsigned c4 = (unsigned)(4 * tc_uniform(lda) * 8);
+  const unsigned c0 = (unsigned)((wm * 64 + orow) * lda * 8 + (wn * 64 + ocol) * 8);
+  // offset of the lane's first row of group i, made anew for each use: kept,
+  // the 16 of them take the registers that the groups need
+  auto first = [&](int i) {
+    unsigned o = c0 + 4 * i * c4;
+    asm volatile("" : "+v"(o));
+    return o;
+  };
+  auto cload = [&](tc_d2(&v)[8], int i, int q0 = 0, int q1 = 4) {
+    unsigned o = first(i) + q0 * c4;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = wm * 64 + i * 16 + 4 * q + orow;
-        const double* rp = cb + (int64_t)(r < mr ? r : mr - 1) * lda;
-        v[2 * q] = *(const tc_d2*)rp;
-        v[2 * q + 1] = *(const tc_d2*)(rp + 32);
-      }
-    };
-    auto cstore = [&](const tc_d2(&v)[8], int i) {
+    for (int q = q0; q < q1; ++q, o += c4) {
+      v[2 * q] = cr.ld2(o, 0);
+      v[2 * q + 1] = cr.ld2(o, 256);
+    }
+  };
+  tc_d2 v0[8], v1[8];
+  if (nch > 0) {
+    high((nch - 1) & 1);
+    products(La, Lb);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (pairs) cload(v0, 0, 0, 2);
+  __builtin_amdgcn_sched_barrier(0);
+  if (nch > 0) products(Ha, Hb);
+  __builtin_amdgcn_sched_barrier(0);
+  if (pairs) {
+    auto sub = [&](tc_d2(&v)[8], int i) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = wm * 64 + i * 16 + 4 * q + orow;
-        double* rp = cb + (int64_t)r * lda;
-        if (r >= mr) continue;
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int j = 0; j < 4; j += 2) {
-          const int c = wn * 64 + 16 * j + ocol;
-          const tc_d2 x = {v[2 * q + j / 2].x - acc[i][j][q], v[2 * q + j / 2].y - acc[i][j + 1][q]};
-          if (!diag || r > c)
-            tc_st2<SHARED>(rp + 16 * j, x.x, x.y);
-          else if (r == c)
-            tc_st<SHARED>(rp + 16 * j, x.x);
+          tc_d2& x = v[2 * q + j / 2];
+          x.x = x.x - acc[i][j][q];
+          x.y = x.y - acc[i][j + 1][q];
         }
-      }
     };
-    cload(cv[0], 0);
+    // a diagonal block stores the pairs below the diagonal; those on it lose
+    // their second element, and are stored last, as a branch between the
+    // groups would let the compiler move the subtractions behind it
+    const int below = (wm - wn) * 64 + orow - ocol;  // r - c of the lane's first pair
+    auto cstore = [&](const tc_d2(&v)[8], int i) {
+      unsigned o = first(i);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i + 1 < 4) cload(cv[(i + 1) & 1], i + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      cstore(cv[i & 1], i);
+      for (int q = 0; q < 4; ++q, o += c4)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2)
+          cr.st2<SHARED>(!diag || below + 16 * i + 4 * q - 16 * j > 0, o, 128 * j, v[2 * q + j / 2]);
+    };
+    auto cstore1 = [&](const tc_d2(&v)[8], int i) {
+      unsigned o = first(i);
+#pragma unroll
+      for (int q = 0; q < 4; ++q, o += c4)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2)
+          cr.st1<SHARED>(below + 16 * i + 4 * q - 16 * j == 0, o, 128 * j, v[2 * q + j / 2].x);
+    };
+    tc_d2 v2[8], v3[8];
+    cload(v0, 0, 2, 4);
+    cload(v1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    sub(v0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    cload(v2, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    sub(v1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    cload(v3, 3);
+    __builtin_amdgcn_sched_barrier(0);
+    cstore(v0, 0);
+    cstore(v1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    sub(v2, 2);
+    cstore(v2, 2);
+    sub(v3, 3);
+    cstore(v3, 3);
+    if (diag) {
+      cstore1(v0, 0);
+      cstore1(v1, 1);
+      cstore1(v2, 2);
+      cstore1(v3, 3);
     }
   } else {
     // ragged: the same pipeline, loads from clamped (in-block) positions,
