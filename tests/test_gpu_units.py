@@ -102,3 +102,24 @@ def test_solve_forms_agree(tc):
     eta = (R.abs().amax(0) / (A.abs().sum(1).max() * X.abs().amax(0) + B.abs().amax(0))).max().item()
     print(f"eta {eta:.2e}")
     assert eta <= 1e-12
+
+
+def test_server_residual_rows(tc):
+    """The reported backward error at the edges of the residual's 16-row
+    blocks and 16 column parts.  The host's residual has the kernel matrix
+    with entries a few ulp apart and sums in another order: the two differ by
+    at most 4 (n + 8) 2^-53, relative to the same denominator."""
+    import torch
+    rng = np.random.default_rng(11)
+    reqs = [(rng.random((n, 2)), rng.standard_normal((n, k)))
+            for n, k in ((1, 1), (2, 8), (15, 3), (16, 1), (17, 8), (31, 2), (33, 4), (65, 5), (150, 8))]
+    with tc.Server(torch.empty(1 << 30, dtype=torch.uint8, device="cuda"), 256 << 20, "continuous") as srv:
+        ids = [srv.submit(p, B, 0.2, 1e-2, 1e-12) for p, B in reqs]
+        for rid, (p, B) in zip(ids, reqs):
+            st, X, eta, _, _ = srv.wait(rid)
+            assert st == tc.CHOL_OK
+            d = p[:, None, :] - p[None, :, :]
+            A = np.exp(-(d * d).sum(-1) / (2 * 0.2 ** 2)) + 1e-2 * np.eye(len(p))
+            eh = oracle.backward_error(A, X, B)
+            print(f"n={len(p)} nrhs={B.shape[1]}: reported {eta:.2e}, host {eh:.2e}")
+            assert abs(eta - eh) <= 4 * (len(p) + 8) * 2.0 ** -53
