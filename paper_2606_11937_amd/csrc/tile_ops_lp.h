@@ -127,15 +127,17 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
   const E* src = (const E*)tc_uniform((int64_t)(ws < 2 ? PA : PB));
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)src, (short)0, (int)((int64_t)nrow * rowb), 0x00020000);
-  const int rl0 = (w & 1) * 64 + (lane >> 3);
-  const unsigned vof0 = (unsigned)(rl0 * rowb + 16 * ((lane & 7) ^ tc_swz(rl0)));
-  const unsigned rowstep = (unsigned)(8 * rowb);
+  const bool isb = ws >= 2;  // rows of B in the order of tc_pair_row
+  const int rl0 = (w & 1) * 64 + (isb ? 2 : 1) * (lane >> 3);
+  const int kl0 = (lane & 7) ^ (lane >> 3);
+  const unsigned vof0 = (unsigned)(rl0 * rowb + 16 * kl0);
+  auto rowof = [&](int q) { return isb ? tc_pair_row(q >> 1, 8 * (q & 1)) : 8 * q; };  // from rl0
   auto stage_load = [&](int st, int k0) {
 #pragma unroll
     for (int q = 0; q < 8; ++q)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rsrc, (tc_lds_void*)((char __attribute__((address_space(3)))*)(tc_lds_void*)lds + st * 32768 + (ws * 8 + q) * 1024),
-          16, vof0 + q * rowstep, (unsigned)(k0 * (int)sizeof(E)), 0, 0);
+          16, vof0 + (unsigned)rowof(q) * (unsigned)rowb, (unsigned)(k0 * (int)sizeof(E)), 0, 0);
   };
   // the ragged last chunk: guarded element loads, zero past kd or past the
   // block's rows, stored where the direct loads would put them
@@ -143,9 +145,8 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
     const E* gb = w < 2 ? PA : PB;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int r = rl0 + q * 8;
-      const int j = (lane & 7) ^ tc_swz(r);
-      const int k = k0 + EPS * j;
+      const int r = rl0 + rowof(q);
+      const int k = k0 + EPS * kl0;
       const E* src = gb + (int64_t)(r < nrow ? r : 0) * ldp + k;
       E v[EPS];
 #pragma unroll
@@ -184,73 +185,121 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
       Lb[i] = rd(0, 1, i, 0);
     }
   }
-  for (int c = 0; c < nch; ++c) {
+  auto high = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Ha[i] = rd(st, 0, i, 1);
+      Hb[i] = rd(st, 1, i, 1);
+    }
+  };
+  auto products = [&](const tc_u4(&fa)[4], const tc_u4(&fb)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = tc_mfma_lp<PREC>(fa[i], fb[j], acc[i][j]);
+  };
+  for (int c = 0; c + 1 < nch; ++c) {
     const int st = c & 1;
+    if (active) {
+      high(st);
+      products(La, Lb);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    if (c + 2 < nch) stage(st, c + 2, nfull);
     if (active) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        Ha[i] = rd(st, 0, i, 1);
-        Hb[i] = rd(st, 1, i, 1);
+        La[i] = rd(st ^ 1, 0, i, 0);
+        Lb[i] = rd(st ^ 1, 1, i, 0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = tc_mfma_lp<PREC>(La[i], Lb[j], acc[i][j]);
-    }
-    if (c + 1 < nch) {
-      __builtin_amdgcn_s_waitcnt(0x0070);
-      __builtin_amdgcn_s_barrier();
-      if (c + 2 < nch) stage(st, c + 2, nfull);
-      if (active) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          La[i] = rd(st ^ 1, 0, i, 0);
-          Lb[i] = rd(st ^ 1, 1, i, 0);
-        }
-      }
-    }
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = tc_mfma_lp<PREC>(Ha[i], Hb[j], acc[i][j]);
+      products(Ha, Hb);
     }
   }
   if (!active) return;
 
-  // epilogue as in tc_update_block: each 16-row group of C is loaded ahead of
-  // the previous group's stores (a ragged block from clamped positions, with
-  // its stores guarded)
-  const int orow = (lane >> 4) * 4, ocol = lane & 15;
-  if (mr == 128 && mc == 128) {
-    double* cb = C + (int64_t)(wm * 64 + orow) * lda + wn * 64 + ocol;
-    double cv[2][16];
-    auto cload = [&](double(&v)[16], int i) {
+  // the last chunk and C -= acc as in tc_update_block, with two of the four
+  // row groups read ahead of the last chunk's products (the accumulators take
+  // half the registers here).  Measured against a group at a time, 8 bytes a
+  // lane: order 16384 in FP32 with its refinement 27.1 -> 26.9 ms.
+  const int orow = (lane >> 4) * 4, ocol = 2 * (lane & 15);
+  const bool pairs = mc == 128;
+  const TcRows cr(C, lda, mr);
+  const unsigned c1 = (unsigned)(tc_uniform(lda) * 8);
+  const unsigned c0 = (unsigned)((wm * 64 + orow) * lda * 8 + (wn * 64 + ocol) * 8);
+  auto first = [&](int i) {
+    unsigned o = c0 + 16 * i * c1;
+    asm volatile("" : "+v"(o));
+    return o;
+  };
+  auto cload = [&](tc_d2(&v)[8], int i) {
+    unsigned o = first(i);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double* rp = cb + (int64_t)(i * 16 + q) * lda;
+    for (int q = 0; q < 4; ++q, o += c1) {
+      v[2 * q] = cr.ld2(o, 0);
+      v[2 * q + 1] = cr.ld2(o, 256);
+    }
+  };
+  tc_d2 v0[8], v1[8];
+  if (pairs) {
+    cload(v0, 0);
+    cload(v1, 1);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (nch > 0) {
+    high((nch - 1) & 1);
+    products(La, Lb);
+    products(Ha, Hb);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (pairs) {
+    const int below = (wm - wn) * 64 + orow - ocol;  // r - c of the lane's first pair
+    auto sub = [&](tc_d2(&v)[8], int i) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[4 * q + j] = rp[16 * j];
-      }
-    };
-    auto cstore = [&](const double(&v)[16], int i) {
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double* rp = cb + (int64_t)(i * 16 + q) * lda;
-        const int r = wm * 64 + i * 16 + orow + q;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
-          if (!diag || r >= c) tc_st<SHARED>(rp + 16 * j, v[4 * q + j] - (double)acc[i][j][q]);
+        for (int j = 0; j < 4; j += 2) {
+          tc_d2& x = v[2 * q + j / 2];
+          x.x = x.x - (double)acc[i][j][q];
+          x.y = x.y - (double)acc[i][j + 1][q];
         }
-      }
     };
-    cload(cv[0], 0);
+    auto cstore = [&](const tc_d2(&v)[8], int i) {
+      unsigned o = first(i);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i + 1 < 4) cload(cv[(i + 1) & 1], i + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      cstore(cv[i & 1], i);
+      for (int q = 0; q < 4; ++q, o += c1)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2)
+          cr.st2<SHARED>(!diag || below + 16 * i + q - 16 * j > 0, o, 128 * j, v[2 * q + j / 2]);
+    };
+    auto cstore1 = [&](const tc_d2(&v)[8], int i) {
+      unsigned o = first(i);
+#pragma unroll
+      for (int q = 0; q < 4; ++q, o += c1)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2)
+          cr.st1<SHARED>(below + 16 * i + q - 16 * j == 0, o, 128 * j, v[2 * q + j / 2].x);
+    };
+    tc_d2 v2[8], v3[8];
+    cload(v2, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    sub(v0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    cload(v3, 3);
+    __builtin_amdgcn_sched_barrier(0);
+    cstore(v0, 0);
+    sub(v1, 1);
+    cstore(v1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    sub(v2, 2);
+    cstore(v2, 2);
+    sub(v3, 3);
+    cstore(v3, 3);
+    if (diag) {
+      cstore1(v0, 0);
+      cstore1(v1, 1);
+      cstore1(v2, 2);
+      cstore1(v3, 3);
     }
   } else {
     // ragged: loads from clamped (in-block) positions, stores guarded
@@ -262,7 +311,7 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
         const double* rp = C + (int64_t)(r < mr ? r : mr - 1) * lda;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
+          const int c = wn * 64 + 32 * (j >> 1) + ocol + (j & 1);
           v[4 * q + j] = rp[c < mc ? c : mc - 1];
         }
       }
@@ -273,7 +322,7 @@ __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const
         const int r = wm * 64 + i * 16 + orow + q;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int c = wn * 64 + j * 16 + ocol;
+          const int c = wn * 64 + 32 * (j >> 1) + ocol + (j & 1);
           if (r < mr && c < mc && (!diag || r >= c))
             tc_st<SHARED>(C + (int64_t)r * lda + c, v[4 * q + j] - (double)acc[i][j][q]);
         }
