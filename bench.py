@@ -76,8 +76,8 @@ TRAFFIC = {
     ("fork_join", 32768, 1024): (14691539678,
                                  "d285ac6b36ad61e52db4c46962ddea1ee97ebb3f000c665c0fc2dbd841f6e989"),
     # lookahead: the bulk of one step (its pool launch and tail summed)
-    ("fork_join_lookahead", 32768, 1024): (12910698553,
-                                           "fced0e1f0915ab1cf65b20f775ecc1d5b85f7826684ae574dff6cbfa456fb38d"),
+    ("fork_join_lookahead", 32768, 1024): (13416949907,
+                                           "1aa0c32079a02e7b25a04f42134cbf438851b7525eb701bd9fb9940eede78702"),
 }
 # the device code the counters describe: the tile bodies, the DAG decode, the
 # fork-join kernels (unit runners up to the naive variant) of kernels.hip,

@@ -684,7 +684,8 @@ __device__ __forceinline__ void tc_subst16(tc_v4d (&x)[NS], const TcMicro& o) {
 // substitutions (about 800 cycles each) per strip, 17000 cycles of the 28000
 // that 64 rows take alone on a CU.  In-kernel time of one workgroup: 11.9 us
 // for 64 rows (23.5 us with one row per lane in the substitution and the
-// operands of L from global memory), 20.8 us for 128 (43.6).
+// operands of L from global memory), 20.8 us for 128 (43.6; 40 with two of
+// them on every CU and their rows in HBM).
 // ---------------------------------------------------------------------------
 struct alignas(16) TcTrsmSmem {
   double op[28][256];     // L_bc, c < b, at b (b - 1) / 2 + c: [q / 2][lane][q % 2] = L_bc[lane % 16][4 q + lane / 16]
@@ -924,8 +925,8 @@ __device__ __forceinline__ void tc_trsm_rows(double* __restrict__ X, const doubl
 // right-looking over 16-column blocks b, and copied back once:
 //   1. diagonal block (b, b): unblocked factorization in registers by wave 0
 //      (lane i holds row i; right-looking over the block's columns, the
-//      POTRF definition on the block; the pivot and the column entries each
-//      step needs are read from their owner lanes);
+//      POTRF definition on the block; a column's entries reach the other
+//      lanes as broadcast operands of the FMAs);
 //   2. blocks (i, b), i > b: forward substitution against L_bb (tc_subst16):
 //      wave 0 takes block b + 1, waves 1 .. 3 two of the others each;
 //   3. blocks (i, j), b < j <= i: A_ij -= L_ib L_jb^T (MFMA, K = 16).
