@@ -1496,7 +1496,7 @@ int tc_launch_factor(double* A, int64_t n, int64_t lda, int64_t T, int sched_fla
     return tc_chk(hipGetLastError());
   }
   if (sched == 4) {
-    hipLaunchKernelGGL(tc_fill_zero, dim3(1), dim3(256), 0, st, (int32_t*)ws.offs, (int64_t)(2 * (g.M + 1)));
+    // (the steps' unit counters, in ws.offs, are clear with the rest)
     tc_timed(TC_UNIT_POTRF, st, [&] {
       hipLaunchKernelGGL(tc_fj_potrf, dim3(1), dim3(TC_THREADS), 0, st, A, lda, g, 0, 0, ws);
     });
