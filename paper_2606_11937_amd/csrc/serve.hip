@@ -166,6 +166,8 @@ __global__ __launch_bounds__(SRV_THREADS) void srv_residual(const SrvDesc* __res
   }
 }
 
+// The items' backward errors: zero only for b = 0 and x = 0; a residual or a
+// solution that is not finite gives NaN, which is above every tolerance.
 __global__ void srv_eta(const SrvDesc* __restrict__ items, int64_t count) {
   const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (q >= count) return;
@@ -173,7 +175,7 @@ __global__ void srv_eta(const SrvDesc* __restrict__ items, int64_t count) {
   double worst = 0.0;
   for (int c = 0; c < d.nrhs; ++c) {
     const double den = d.stats[0] * d.stats[1 + d.nrhs + c] + d.stats[1 + 2 * d.nrhs + c];
-    const double e = den > 0.0 ? d.stats[1 + c] / den : 0.0;
+    const double e = den == 0.0 ? 0.0 : d.stats[1 + c] / den;
     worst = e > worst || e != e ? e : worst;
   }
   d.stats[1 + 3 * d.nrhs] = worst;
