@@ -1,5 +1,6 @@
-// gptr.h -- global-address-space view of a pointer value read from memory.
+// gptr.h -- small device helpers that several sources share.
 //
+// tc_global: the global-address-space view of a pointer value read from memory.
 // A pointer loaded from a descriptor (in LDS or in global memory) is
 // generic, and every access through it becomes a flat instruction, which
 // the compiler can only wait for with both memory counters drained: each
@@ -19,3 +20,7 @@ __device__ __forceinline__ T* tc_global(T* p) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(v >> 32));
   return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
+
+// The larger of two values, or the NaN among them: fmax drops a NaN, and a
+// maximum that decides whether a result is accepted must keep it.
+__device__ __forceinline__ double tc_max_nan(double a, double b) { return b > a || b != b ? b : a; }

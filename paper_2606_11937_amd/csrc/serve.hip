@@ -113,7 +113,8 @@ __device__ __forceinline__ void srv_atomic_max(double* p, double v) {
 // Matrix-free residual R = B - A X and its statistics; grid (row blocks of
 // 16, items).  Thread (row r, part p) sums columns j = p, p + 16, ... of row
 // i = 16 block + r; the sixteen parts are combined in a fixed order, and the
-// four rows of a wave take their maxima before the one atomic per statistic.
+// four rows of a wave take their maxima before the one atomic per statistic
+// (rows past n count as zero, so a NaN beside them has to win).
 // Bound by the chain of exponentials of a thread, n / 16 of them, on a chip
 // that a few items do not fill: four parts a row (four times the chain, a
 // quarter of the workgroups, an atomic a row on the same few words) took
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(SRV_THREADS) void srv_residual(const SrvDesc* __res
     return v;
   };
   auto wave_max = [&](double* at, double v) {
-    v = fmax(v, __shfl_xor(v, 16));
-    v = fmax(v, __shfl_xor(v, 32));
+    v = tc_max_nan(v, __shfl_xor(v, 16));
+    v = tc_max_nan(v, __shfl_xor(v, 32));
     if ((threadIdx.x & 63) == 0) srv_atomic_max(at, v);
   };
   wave_max(d.stats, sum16(rs));

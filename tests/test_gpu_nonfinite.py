@@ -1,5 +1,5 @@
 """A solution that is not finite is never reported as converged: the backward
-error of a NaN solution is NaN."""
+error of an overflowed or NaN solution is NaN."""
 from __future__ import annotations
 
 import numpy as np
@@ -25,8 +25,19 @@ def served(tc, pts, B, mode="continuous"):
     return st, X, eta
 
 
-@pytest.mark.parametrize("n,nrhs", [(65, 1), (65, 8), (200, 3)])
+@pytest.mark.parametrize("mode", ["continuous", "fifo"])
+def test_server_overflowed_solution(tc, mode):
+    """Two coincident points, A = [[1.01, 1], [1, 1.01]], and b of 1.7e308:
+    x overflows, b - A x is NaN in both rows, and the residual's wave holds
+    two rows past the matrix beside them."""
+    st, X, eta = served(tc, np.zeros((2, 2)), np.array([[1.7e308], [-1.7e308]]), mode)
+    assert not np.isfinite(X).any()
+    assert st == tc.CHOL_NOT_CONVERGED and np.isnan(eta)
+
+
+@pytest.mark.parametrize("n,nrhs", [(1, 1), (3, 2), (65, 1), (65, 8), (200, 3)])
 def test_server_nan_right_hand_side(tc, n, nrhs):
+    """One or three rows leave rows past the matrix in the residual's only wave."""
     rng = np.random.default_rng(n)
     B = rng.standard_normal((n, nrhs))
     B[n // 2, nrhs - 1] = np.nan
