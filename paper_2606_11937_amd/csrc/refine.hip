@@ -30,6 +30,7 @@
 
 #include <vector>
 
+#include "gptr.h"
 #include "launch.h"
 
 #define RF_THREADS 256
@@ -147,7 +148,7 @@ __device__ __forceinline__ double rf_block_reduce(double v, bool take_max) {
   for (int s = RF_THREADS / 2; s > 0; s >>= 1) {
     if ((int)threadIdx.x < s) {
       const double o = red[threadIdx.x + s];
-      red[threadIdx.x] = take_max ? fmax(red[threadIdx.x], o) : red[threadIdx.x] + o;
+      red[threadIdx.x] = take_max ? tc_max_nan(red[threadIdx.x], o) : red[threadIdx.x] + o;
     }
     __syncthreads();
   }
@@ -156,11 +157,11 @@ __device__ __forceinline__ double rf_block_reduce(double v, bool take_max) {
   return r;
 }
 
-// out[c] = max_i |U[i][c]| (one workgroup per column c).
+// out[c] = max_i |U[i][c]|, or NaN if an entry is (one workgroup per column c).
 __global__ __launch_bounds__(RF_THREADS) void rf_colmax(const double* U, int64_t ldu, int64_t n, double* out) {
   const int64_t c = blockIdx.x;
   double m = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += RF_THREADS) m = fmax(m, fabs(U[i * ldu + c]));
+  for (int64_t i = threadIdx.x; i < n; i += RF_THREADS) m = tc_max_nan(m, fabs(U[i * ldu + c]));
   m = rf_block_reduce(m, true);
   if (threadIdx.x == 0) out[c] = m;
 }
@@ -176,13 +177,14 @@ __global__ __launch_bounds__(RF_THREADS) void rf_coldot(const double* U, int64_t
   if (threadIdx.x == 0) out[c] = s;
 }
 
-// eta[c] = rmax[c] / (anorm xmax[c] + bmax[c]) (0 when the denominator is 0).
+// eta[c] = rmax[c] / (anorm xmax[c] + bmax[c]) (0 when the denominator is 0,
+// NaN when the residual or the solution is not finite).
 __global__ void rf_eta(const double* rmax, const double* xmax, const double* bmax, const double* anorm, int64_t nrhs,
                        double* eta) {
   const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (c >= nrhs) return;
   const double den = anorm[0] * xmax[c] + bmax[c];
-  eta[c] = den > 0.0 ? rmax[c] / den : 0.0;
+  eta[c] = den == 0.0 ? 0.0 : rmax[c] / den;
 }
 
 // ------------------------------------------------------- elementwise steps

@@ -44,3 +44,22 @@ def test_server_nan_right_hand_side(tc, n, nrhs):
     st, X, eta = served(tc, rng.random((n, 2)), B)
     assert np.isnan(X[:, nrhs - 1]).any()
     assert st == tc.CHOL_NOT_CONVERGED and np.isnan(eta)
+
+
+@pytest.mark.parametrize("method", ["ir", "pcg"])
+@pytest.mark.parametrize("n", [1, 65, 300])
+def test_refine_nan_column(tc, method, n):
+    """One NaN column: its backward error is NaN and the call not converged;
+    the other columns meet the tolerance."""
+    import torch
+    from paper_2606_11937_amd import inputs
+    A = torch.from_numpy(inputs.gg_plus_identity(n, seed=n)).cuda()
+    L = A.clone()
+    assert tc.chol_factor_mixed(L, 128, "fp32") == 0
+    B = torch.from_numpy(np.random.default_rng(n).standard_normal((n, 3))).cuda()
+    B[n // 2, 1] = float("nan")
+    X = torch.zeros_like(B)
+    ok, it, eta = tc.chol_solve_refine(A, L, B, X, 128, method, 1e-12, 5)
+    print(f"{method} n={n}: converged {ok} after {it}, eta {eta}")
+    assert not ok and np.isnan(eta[1])
+    assert eta[0] <= 1e-12 and eta[2] <= 1e-12
