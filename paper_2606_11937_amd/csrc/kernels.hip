@@ -823,7 +823,7 @@ __device__ __forceinline__ TcWs tc_global_ws(const TcWs& w) {
 // transposed from the lower triangle), and thread (row r, part p) sums its
 // 16 columns of every tile in order; the four parts are added in order
 // p = 0..3.  Deterministic.  Returns, in red[0..3] (LDS, after a barrier),
-// max |r_i|, max |x_i|, max |b0_i| and max_i sum_j |A0_ij|.
+// max |r_i|, max |x_i|, max |b0_i| and max_i sum_j |A0_ij| (NaN if an entry is).
 struct TcResSmem {
   double t[64][65];
   double xs[64];
@@ -876,10 +876,10 @@ __device__ __forceinline__ void tc_wg_residual(const double* __restrict__ A0, in
       const double as = sm.apart[0][rr] + sm.apart[1][rr] + sm.apart[2][rr] + sm.apart[3][rr];
       const double bi = b0[i], ri = bi - sum;
       r[i] = ri;
-      rmax = fmax(rmax, fabs(ri));
-      xmax = fmax(xmax, fabs(x[i]));
-      bmax = fmax(bmax, fabs(bi));
-      amax = fmax(amax, as);
+      rmax = tc_max_nan(rmax, fabs(ri));
+      xmax = tc_max_nan(xmax, fabs(x[i]));
+      bmax = tc_max_nan(bmax, fabs(bi));
+      amax = tc_max_nan(amax, as);
     }
     __syncthreads();
   }
@@ -890,7 +890,7 @@ __device__ __forceinline__ void tc_wg_residual(const double* __restrict__ A0, in
   __syncthreads();
   if (tid < 4) {
     double m = 0.0;
-    for (int t = 0; t < TC_THREADS; ++t) m = fmax(m, sm.red[tid][t]);
+    for (int t = 0; t < TC_THREADS; ++t) m = tc_max_nan(m, sm.red[tid][t]);
     sm.red[tid][0] = m;
   }
   __syncthreads();
@@ -929,7 +929,7 @@ __device__ __forceinline__ void tc_wg_solve_unit(const double* __restrict__ L, i
     }
     tc_wg_residual(A0, lda0, n, B, b0, R, sm.r);
     const double den = sm.r.red[3][0] * sm.r.red[1][0] + sm.r.red[2][0];
-    eta = tc_uniform(den > 0.0 ? sm.r.red[0][0] / den : 0.0);
+    eta = tc_uniform(den == 0.0 ? 0.0 : sm.r.red[0][0] / den);  // (NaN if r or x is not finite)
     __syncthreads();
     if (!(eta > tol) || p >= max_iter) break;
   }

@@ -63,3 +63,22 @@ def test_refine_nan_column(tc, method, n):
     print(f"{method} n={n}: converged {ok} after {it}, eta {eta}")
     assert not ok and np.isnan(eta[1])
     assert eta[0] <= 1e-12 and eta[2] <= 1e-12
+
+
+def test_refined_batch_nan_right_hand_side(tc):
+    """The matrices with a NaN in b report a NaN backward error, the others
+    meet the tolerance."""
+    import torch
+    from paper_2606_11937_amd import inputs
+    ns = [1, 3, 64, 65, 200, 300]
+    As = [torch.from_numpy(inputs.gg_plus_identity(n, seed=n)).cuda() for n in ns]
+    Ls = [torch.empty_like(a) for a in As]
+    Bs = [torch.from_numpy(np.random.default_rng(n).standard_normal(n)).cuda() for n in ns]
+    for k in (0, 1, 3, 5):
+        Bs[k][ns[k] // 2] = float("nan")
+    Xs = [torch.empty_like(b) for b in Bs]
+    infos, its, etas = tc.chol_factor_solve_batched_mixed(As, Ls, Bs, Xs, precs=["fp64", "fp32"] * 3)
+    print(f"infos {infos} corrections {its} etas {etas}")
+    assert infos == [0] * len(ns)
+    for k, e in enumerate(etas):
+        assert np.isnan(e) if k in (0, 1, 3, 5) else e <= 1e-12
