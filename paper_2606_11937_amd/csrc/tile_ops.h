@@ -1303,10 +1303,13 @@ __device__ __forceinline__ int tc_syrk_block(double* __restrict__ C, const doubl
   };
   // chunk c has landed when at most the loads of c + 1 and c + 2 are
   // outstanding (s_waitcnt encodings: 0x0F78 = vmcnt(8), 0x0F74 = vmcnt(4),
-  // 0x0F70 = vmcnt(0)); the barrier behind the wait publishes it and, because
-  // every wave has read chunk c - 1 by then, frees that chunk's stage
+  // 0x0F70 = vmcnt(0)); the barrier behind the wait publishes it.  It also
+  // frees chunk c - 1's stage, so each wave first waits for its LDS reads
+  // (0xC07F = lgkmcnt(0)): the last fragment read may have no product that
+  // would wait for it, and nothing else keeps a product in front of a barrier
   auto publish = [] {
     asm volatile("" ::: "memory");  // no LDS read moves across the barrier
+    __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
