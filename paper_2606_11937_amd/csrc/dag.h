@@ -332,3 +332,22 @@ TC_HD void tc_unit_publish_with(const TcGeom& g, int32_t* pdone, int32_t* ver, c
     add(pdone + tc_gid(g, u.J, u.a));
   }
 }
+
+// Whether the lookahead schedule runs a step's trailing update of `units`
+// units as one launch of a workgroup each (cap: workgroups that fit on the
+// chip at once) instead of splitting it over two streams: where the split
+// costs more than it hides.  That is when all its units fit on the chip, and
+// with tiles of one sub-column, whose next panel is a single TRSM launch of
+// 15-25 us, about what the two events and the pool's two launches cost.
+// Measured (factor ms, always split -> this rule): T=128: n=3001 2.31 -> 1.52,
+// 8192 9.3 -> 6.9, 16384 42.9 -> 37.8, 32768 270.7 -> 265.6; units <= cap:
+// T=256, n=4096 2.67 -> 2.39; T=512, n=8192 7.05 -> 6.8; T=1024, n=16384
+// 29.9 -> 29.6, n=32768 unchanged.  From 2 cap on the split is the better one
+// at T >= 512 (n=16384, T=1024: 30.2 at 4 cap).
+// A grid holds at most 2^32 - 1 threads; small tiles of a large matrix have
+// more units than that allows (T=1 from n=5794, T=16 from n=92689), which
+// the pool's fixed grid takes.
+#define TC_MAX_GRID (0xFFFFFFFFll / 256)  // workgroups of 256 threads
+TC_HD bool tc_update_whole(const TcGeom& g, int64_t units, int64_t cap) {
+  return units <= TC_MAX_GRID && (units <= cap || g.SB == 1);
+}

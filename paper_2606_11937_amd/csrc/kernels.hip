@@ -1366,7 +1366,7 @@ static int64_t tc_pool_grid_size();
 // The bulk runs as a pool on a per-step unit counter: on B with `reserve`
 // workgroup slots left free for A's panel chain, then on A behind the next
 // step's chain, into the slots the chain frees.  Steps whose update is small
-// run it as one launch (the rule is in the loop).  Unit bodies and per-block
+// run it as one launch (tc_update_whole, dag.h).  Unit bodies and per-block
 // update order are the fork-join ones, so the factor is bit-identical to
 // every other schedule.
 // before(J) runs on A once panel J is final, ahead of step J's updates
@@ -1416,17 +1416,7 @@ static int tc_lookahead_steps(double* A, int64_t lda, const TcGeom& g, TcWs ws, 
     if (!before(J)) return TC_LAUNCH_EDEVICE;
     const int64_t ncol = tc_colsize(g, J + 1);  // units of tile column J+1 at step J
     if (b_used && hipStreamWaitEvent(st, eb, 0) != hipSuccess) return TC_LAUNCH_EDEVICE;  // B's bulk J-1
-    // One launch for the whole update of the step, on the caller's stream,
-    // where splitting it costs more than it hides: when all its units fit on
-    // the chip at once, and with tiles of one sub-column, whose next panel is
-    // a single TRSM launch of 15-25 us, about what the two events and the
-    // pool's two launches cost.  Measured (factor ms, always split -> this
-    // rule): T=128: n=3001 2.31 -> 1.52, 8192 9.3 -> 6.9, 16384 42.9 -> 37.8,
-    // 32768 270.7 -> 265.6; units <= cap: T=256, n=4096 2.67 -> 2.39; T=512,
-    // n=8192 7.05 -> 6.8; T=1024, n=16384 29.9 -> 29.6, n=32768 unchanged.
-    // From 2 cap on the split is the better one at T >= 512 (n=16384,
-    // T=1024: 30.2 at 4 cap).
-    if (nu <= cap || g.SB == 1) {
+    if (tc_update_whole(g, nu, cap)) {  // one launch, on the caller's stream
       tc_timed(TC_UNIT_UPDATE, st, [&] { range(J, nu); });
       continue;
     }
