@@ -148,7 +148,7 @@ __device__ __forceinline__ void tc_run_update(double* A, int64_t lda, const TcGe
   const int64_t ri = tc_row0(g, u.I, u.a);
   const int64_t rk = tc_row0(g, u.K, u.b);
   const int64_t cj = (int64_t)u.J * g.T;
-  tc_update_block(A + ri * lda + rk, A + ri * lda + cj, A + rk * lda + cj, lda, tc_rows(g, u.I, u.a),
+  tc_update_block<false>(A + ri * lda + rk, A + ri * lda + cj, A + rk * lda + cj, lda, tc_rows(g, u.I, u.a),
                   tc_rows(g, u.K, u.b), (int)tc_tdim(g, u.J), ri == rk, sm);
 }
 
@@ -158,7 +158,7 @@ __device__ __forceinline__ void tc_run_panel(double* A, int64_t lda, const TcGeo
   const int64_t ri = tc_row0(g, u.I, u.a);
   const int64_t rt = tc_row0(g, u.J, u.b);
   const int64_t cs = tc_row0(g, u.J, u.K);
-  tc_update_block(A + ri * lda + rt, A + ri * lda + cs, A + rt * lda + cs, lda, tc_rows(g, u.I, u.a),
+  tc_update_block<false>(A + ri * lda + rt, A + ri * lda + cs, A + rt * lda + cs, lda, tc_rows(g, u.I, u.a),
                   tc_rows(g, u.J, u.b), tc_rows(g, u.J, u.K), ri == rt, sm);
 }
 
@@ -211,7 +211,7 @@ __device__ __forceinline__ void tc_run_update_potrf(double* A, int64_t lda, cons
   if (tc_syrk_fits(true, td, kd)) {
     bad = tc_syrk_block<true, false>(D, P, lda, kd, sm.upd, sm.potrf);
   } else {
-    tc_update_block(D, P, P, lda, td, td, kd, true, sm.upd);
+    tc_update_block<false>(D, P, P, lda, td, td, kd, true, sm.upd);
     __syncthreads();
     bad = tc_potrf_tile<false>(D, lda, td, sm.potrf);
   }
@@ -356,7 +356,7 @@ __device__ __forceinline__ void tc_run_update_lp(double* A, int64_t lda, const T
                                                  const typename TcLp<PREC>::elem* P, int64_t ldp, TcUpdSmem& sm) {
   const int64_t ri = tc_row0(g, u.I, u.a);
   const int64_t rk = tc_row0(g, u.K, u.b);
-  tc_update_block_lp<PREC>(A + ri * lda + rk, P + ri * ldp, P + rk * ldp, lda, ldp, tc_rows(g, u.I, u.a),
+  tc_update_block_lp<PREC, false>(A + ri * lda + rk, P + ri * ldp, P + rk * ldp, lda, ldp, tc_rows(g, u.I, u.a),
                            tc_rows(g, u.K, u.b), (int)tc_tdim(g, J), ri == rk, sm);
 }
 
@@ -452,7 +452,10 @@ __global__ __launch_bounds__(TC_THREADS) void tc_unscale_lower(double* A, int64_
 // Dependency test and completion of unit u (the counter rules are in dag.h):
 // the counters are read with relaxed agent-scope atomic loads (the caller
 // issues the acquire fence once the unit is ready) and incremented with
-// relaxed agent-scope atomic adds (after the workgroup's release fence).
+// relaxed agent-scope atomic adds, once tc_unit_stored has seen every store
+// of the unit complete.  There is no release fence at device scope: what
+// another workgroup of the launch reads is stored with tc_st<true>,
+// tc_st2<true> or TcRows' stores with SHARED.
 __device__ __forceinline__ bool tc_unit_ready(const TcGeom& g, const TcWs& ws, const TcUnit& u) {
   return tc_unit_ready_with(g, ws.pdone, ws.ver, u, [](const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -476,8 +479,8 @@ __device__ __forceinline__ void tc_unit_publish(const TcGeom& g, const TcWs& ws,
 // Measured, kernel time, 4096 matrices of orders 32 .. 2048 with a solve
 // each: 38.4 -> 34.5 ms.
 __device__ __forceinline__ void tc_unit_stored() {
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // no store moves behind the wait
+  __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
   __syncthreads();
 }
 

@@ -65,6 +65,8 @@ __device__ __forceinline__ tc_v4d tc_mfma_neg(double a, double b, tc_v4d c) {
 // units are read by workgroups of the same launch on other XCDs: a
 // device-scope store goes through the XCD's L2 to memory, so a finished unit
 // needs no write-back of that L2 before it is published (see tc_unit_stored).
+// Every body takes the choice from its caller, without a default: an ordinary
+// store in a persistent unit would be read stale only now and then.
 template <bool SHARED, class V>
 __device__ __forceinline__ void tc_st(V* p, V v) {
   if constexpr (SHARED)
@@ -171,7 +173,7 @@ struct TcRows {
 // The row of B (and column of C) that LDS row 16 i + r of its 64 holds.
 __device__ __forceinline__ int tc_pair_row(int i, int r) { return 32 * (i >> 1) + 2 * r + (i & 1); }
 
-template <bool SHARED = false>
+template <bool SHARED>
 __device__ __forceinline__ void tc_update_block(double* __restrict__ C, const double* __restrict__ PA,
                                                 const double* __restrict__ PB, int64_t lda, int mr, int mc,
                                                 int kd, bool diag, TcUpdSmem& sm) {

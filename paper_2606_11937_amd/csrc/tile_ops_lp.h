@@ -105,7 +105,7 @@ __device__ __forceinline__ tc_v4f tc_mfma_lp<TC_PREC_BF16>(const tc_u4& a, const
 // Same contract as tc_update_block with PA, PB low-precision rows of leading
 // dimension ldp (elements); mr, mc <= 128.  The shared memory is the FP64
 // kernel's (the same 128 x 128-byte stage layout).
-template <int PREC, bool SHARED = false>
+template <int PREC, bool SHARED>
 __device__ __forceinline__ void tc_update_block_lp(double* __restrict__ C, const typename TcLp<PREC>::elem* __restrict__ PA,
                                                    const typename TcLp<PREC>::elem* __restrict__ PB, int64_t lda,
                                                    int64_t ldp, int mr, int mc, int kd, bool diag, TcUpdSmem& sm) {
