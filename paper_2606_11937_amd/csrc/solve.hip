@@ -23,6 +23,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <type_traits>
+
 #include "gptr.h"
 #include "launch.h"
 
@@ -240,23 +243,79 @@ __device__ __forceinline__ double sv_dot64(const double (&c)[SV_NB], const doubl
   sv_dot16<48>(d, c, y[3]);
   return (d[0] + d[1]) + (d[2] + d[3]);
 }
+// d + sum of c[m] * (y of lane m of the row), m = 0 .. 15 ascending
+__device__ __forceinline__ double sv_dot_row(double d, const double (&c)[16], double y) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c0] row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c1] row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c2] row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c3] row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c4] row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c5] row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c6] row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c7] row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c8] row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c9] row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c10] row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c11] row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c12] row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c13] row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c14] row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %[y], %[c15] row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+&v"(d)
+      : [y] "v"(y), [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]), [c5] "v"(c[5]),
+        [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]), [c11] "v"(c[11]),
+        [c12] "v"(c[12]), [c13] "v"(c[13]), [c14] "v"(c[14]), [c15] "v"(c[15]));
+  return d;
+}
+// Column c of v added over the wave's rows, (row 0 + row 1) + (row 2 + row 3),
+// to the lanes of row c: rows change places between two columns, so that one
+// addition serves both.
+__device__ __forceinline__ double sv_swap_add(double a, double b, bool wide) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const auto p = wide ? __builtin_amdgcn_permlane32_swap(x[h], y[h], false, false)
+                        : __builtin_amdgcn_permlane16_swap(x[h], y[h], false, false);
+    x[h] = p[0];
+    y[h] = p[1];
+  }
+  return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ double sv_sum_rows(const double (&v)[2]) {
+  const double a = sv_swap_add(v[0], v[1], false);
+  return sv_swap_add(a, a, true);
+}
+__device__ __forceinline__ double sv_sum_rows(const double (&v)[4]) {
+  return sv_swap_add(sv_swap_add(v[0], v[1], false), sv_swap_add(v[2], v[3], false), true);
+}
 // The substitution with a unit diagonal: lane k holds its value and its row
 // (column, backward) of the strictly lower (upper) block, zero on and past
 // the diagonal.  Each lane receives its subtractions in ascending
 // (descending) order of the column.
-__device__ __forceinline__ double sv_chain64_fwd(double v, const double (&c)[SV_NB]) {
+// late(0) runs in front of the first group, late(1) behind the second: loads
+// of the coefficients of the third and of the fourth.
+template <class Late>
+__device__ __forceinline__ double sv_chain64_fwd(double v, const double (&c)[SV_NB], Late late) {
+  late(std::integral_constant<int, 0>());
   v = sv_group_up<0>(v, c);
   v = sv_rows_up<0, 0xe>(v, c, sv_row_copy<0>(v));
   v = sv_group_up<1>(v, c);
+  late(std::integral_constant<int, 1>());
   v = sv_rows_up<1, 0xc>(v, c, sv_row_copy<1>(v));
   v = sv_group_up<2>(v, c);
   v = sv_rows_up<2, 0x8>(v, c, sv_row_copy<2>(v));
   return sv_group_up<3>(v, c);
 }
-__device__ __forceinline__ double sv_chain64_bwd(double v, const double (&c)[SV_NB]) {
+template <class Late>
+__device__ __forceinline__ double sv_chain64_bwd(double v, const double (&c)[SV_NB], Late late) {
+  late(std::integral_constant<int, 0>());
   v = sv_group_down<3>(v, c);
   v = sv_rows_down<3, 0x7>(v, c, sv_row_copy<3>(v));
   v = sv_group_down<2>(v, c);
+  late(std::integral_constant<int, 1>());
   v = sv_rows_down<2, 0x3>(v, c, sv_row_copy<2>(v));
   v = sv_group_down<1>(v, c);
   v = sv_rows_down<1, 0x1>(v, c, sv_row_copy<1>(v));
@@ -274,7 +333,8 @@ __device__ __forceinline__ double sv_chain64_bwd(double v, const double (&c)[SV_
 // which no arithmetic result is; an entry with its bit pattern is stored as
 // the default quiet NaN instead.
 // Payload layout: block-major, [block][64 rows][PW columns], PW = 2 for the
-// one- and two-column sweeps and 16 for the others; rows past n and columns
+// one- and two-column sweeps, 4 for passes of four and 16 for the refinement
+// sweeps; rows past n and columns
 // past the right-hand sides are stored as zero.
 #define SV_SENTINEL 0x7FF4A5A5A5A5A5A5ull
 #define SV_QNAN 0x7FF8000000000000ull
@@ -356,81 +416,89 @@ __device__ __forceinline__ void sv_tile_load(const double* __restrict__ L, int64
 // at a time (a row of 66 doubles keeps the reads aligned and off each
 // other's banks).
 #define SV_TS (SV_NB + 2)
+template <int K0, int K1>
 __device__ __forceinline__ void sv_coefs(const double (*T)[SV_TS], int lane, double (&c)[SV_NB]) {
   typedef double d2 __attribute__((ext_vector_type(2), aligned(16)));
 #pragma unroll
-  for (int k = 0; k < SV_NB; k += 2) {
+  for (int k = K0; k < K1; k += 2) {
     const d2 v = *(const d2*)&T[lane][k];
-    c[k] = v.x;
-    c[k + 1] = v.y;
-  }
-}
-__device__ __forceinline__ void sv_coefs(const double (*T)[SV_TS], int lane, double scale, double (&c)[SV_NB]) {
-  sv_coefs(T, lane, c);
-#pragma unroll
-  for (int k = 0; k < SV_NB; ++k) c[k] = c[k] * scale;
-}
-// 64 consecutive doubles of memory
-__device__ __forceinline__ void sv_row_ld(const double* __restrict__ p, double (&c)[SV_NB]) {
-  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
-#pragma unroll
-  for (int k = 0; k < SV_NB; k += 2) {
-    const d2 v = *(const d2*)(p + k);
     c[k] = v.x;
     c[k + 1] = v.y;
   }
 }
 // Pin register values in front of a wait (an empty statement that uses them),
 // so that the compiler does not move the LDS reads behind it.
+template <int K0, int K1>
 __device__ __forceinline__ void sv_pin(double (&c)[SV_NB]) {
 #pragma unroll
-  for (int k = 0; k < SV_NB; ++k) asm volatile("" : "+v"(c[k]));
+  for (int k = K0; k < K1; ++k) asm volatile("" : "+v"(c[k]));
 }
-// The chain wave's wait for block j's payload column (entries p[RC k], k < 64):
-// y[t] of lane l becomes entry 16 t + l % 16, as sv_dot64 takes it.  WIDE:
-// every poll loads the four values of each lane; otherwise one value per lane
-// is polled, a quarter of the traffic when many workgroups wait at once, and
-// copied across the rows; the block before the neighbour (not NEXT) is
-// probed first.
-template <int RC, bool WIDE, bool NEXT>
+// The chain wave's wait for the neighbour's payload column (entries p[RC k],
+// k < 64): y[t] of lane l becomes entry 16 t + l % 16, as sv_dot64 takes it.
+template <int RC>
 __device__ __forceinline__ bool sv_wait_col(const double* p, double (&y)[4], int lane, SvWs* ws, int64_t wait_ticks) {
-  if constexpr (WIDE) {
-    auto load = [&] {
+  auto load = [&] {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) y[t] = sv_pay_ld(p + (16 * t + (lane & 15)) * RC);
-    };
-    load();
-    return sv_wave_wait_full(
-        load, [&] { return sv_pending(y[0]) || sv_pending(y[1]) || sv_pending(y[2]) || sv_pending(y[3]); }, ws,
-        wait_ticks);
-  } else {
-    double v = sv_pay_ld(p + lane * RC);
-    auto load = [&] { v = sv_pay_ld(p + lane * RC); };
-    auto pend = [&] { return sv_pending(v); };
-    const bool got = NEXT ? sv_wave_wait_full(load, pend, ws, wait_ticks)
-                          : sv_wave_wait(p + (SV_NB - 1) * RC, load, pend, ws, wait_ticks);
-    y[0] = sv_row_copy<0>(v);
-    y[1] = sv_row_copy<1>(v);
-    y[2] = sv_row_copy<2>(v);
-    y[3] = sv_row_copy<3>(v);
-    return got;
-  }
+    for (int t = 0; t < 4; ++t) y[t] = sv_pay_ld(p + (16 * t + (lane & 15)) * RC);
+  };
+  load();
+  return sv_wave_wait_full(
+      load, [&] { return sv_pending(y[0]) || sv_pending(y[1]) || sv_pending(y[2]) || sv_pending(y[3]); }, ws,
+      wait_ticks);
+}
+// The product with the block before the neighbour, by all four waves: wave w
+// takes 16 of the 64 entries, lane (row rr, q) of it the terms 4 m + rr of
+// entry 16 w + q (coefficients l[m]) of every column, so the row rr holds the
+// partial sum over k = 4 m + rr that sv_dot64 calls d[rr], and the four are
+// added in its order.  p: the block's payload.
+template <int RC>
+__device__ __forceinline__ bool sv_near_product(const double* p, const double (&l)[16], double (*near)[SV_NB], int w,
+                                                int rr, int q, SvWs* ws, int64_t wait_ticks) {
+  double y[RC];
+  auto load = [&] {
+#pragma unroll
+    for (int c = 0; c < RC; ++c) y[c] = sv_pay_ld(p + (4 * q + rr) * RC + c);
+  };
+  load();
+  if (!sv_wave_wait_full(
+          load,
+          [&] {
+            bool pend = false;
+#pragma unroll
+            for (int c = 0; c < RC; ++c) pend = pend || sv_pending(y[c]);
+            return pend;
+          },
+          ws, wait_ticks))
+    return false;
+  double d[RC];
+#pragma unroll
+  for (int c = 0; c < RC; ++c) d[c] = sv_dot_row(0.0, l, y[c]);
+  const double sum = sv_sum_rows(d);
+  if (rr < RC) near[rr][16 * w + q] = sum;
+  return true;
 }
 
 // The diagonal block strictly lower (zero on and above the diagonal and past
 // nr) and the reciprocals of its diagonal (rows past nr take a unit pivot),
 // from a thread's tile share.
-template <class Put>
-__device__ __forceinline__ void sv_diag_put(const double (&t)[16], int nr, double* rdiag, Put put) {
+__device__ __forceinline__ void sv_rdiag_put(const double (&t)[16], int nr, double* rdiag) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double piv = 1.0;
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int i = w + 4 * q;
-    put(i, lane, (i < nr && lane < i) ? t[q] : 0.0);
     piv = (i == lane && i < nr) ? t[q] : piv;
   }
   if (((lane - w) & 3) == 0) rdiag[lane] = 1.0 / piv;
+}
+template <class Put>
+__device__ __forceinline__ void sv_lower_put(const double (&t)[16], int nr, Put put) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int i = w + 4 * q;
+    put(i, lane, (i < nr && lane < i) ? t[q] : 0.0);
+  }
 }
 
 // ------------------------------------------------- in-block substitution
@@ -464,13 +532,23 @@ __device__ __forceinline__ void sv_chains_fwd(double* v, const double (*Lbb)[SV_
 // ---------------------------------------------------------------- forward
 // y_b = L_bb^{-1} (B_b - sum_{j<b} L_bj y_j), one block per workgroup, up to
 // four right-hand sides.  The four waves fold the blocks j <= b - 3 as their
-// payloads arrive; then wave c (c < nc) takes right-hand side c alone: it
-// waits for y_{b-2} and subtracts L_{b,b-2} y_{b-2}, waits for y_{b-1} and
-// subtracts L_{b,b-1} y_{b-1}, substitutes, and publishes its column, so the
-// last two block steps involve one wave and no workgroup barrier.  (With
-// y_{b-2} in the fold, its probe, load, row sums and barrier took 3 us from
-// its publication to the chain wave, which started late every step: 2.4 us a
-// step, 1.6 us now.)
+// payloads arrive and then form L_{b,b-2} y_{b-2} (sv_near_product, its
+// coefficients in registers since the start); then wave c (c < nc) takes
+// right-hand side c alone: it waits for y_{b-1}, subtracts L_{b,b-1} y_{b-1},
+// substitutes, and publishes its column.
+// What bounds a step is the way from one published block to the next, and
+// everything the chain wave needs besides y_{b-1} is in its place before that
+// arrives: its row of L_{b,b-1} and half of its row of the diagonal block in
+// registers, the other half read from LDS while the first half substitutes.
+// (With y_{b-2} in the fold, its probe, load, row sums and barrier took 3 us
+// from its publication to the chain wave, which started late every step: 2.4
+// us a step, 1.6 us now.)
+// The kernel keeps to 256 registers and to LDS that fits on a CU beside a
+// workgroup of the factorization's kernels, so that a solve on one stream
+// goes on beside a factorization on another.  A form with three coefficient
+// tiles in LDS (104 KB) and up to 512 registers was as fast alone, but beside
+// a fork-join factorization of order 32768 a solve of order 1500 waited up to
+// 14 ms for an empty CU (0.8 ms now).
 // Fold layout: wave w, lane 16 rr + q covers rows 16 s + 4 w + rr (s < 4)
 // of the block and columns 16 m + q (m < 4) of every folded block, so each
 // load instruction reads four whole 128-byte row segments.  A lane
@@ -486,22 +564,27 @@ __device__ __forceinline__ void sv_chains_fwd(double* v, const double (*Lbb)[SV_
 // forward sweep; npass passes of RC columns share the launch, their blocks
 // interleaved in ticket order: ticket g is block g / npass of pass
 // g % npass, and waits only for smaller tickets of its own pass.
-// WIDE: one workgroup on a CU, with three coefficient tiles in LDS and two of
-// them in the chain wave's registers (more than 256) before its wait.
-// Otherwise two workgroups share a CU: two tiles in LDS, L_{b,b-2} read from
-// memory, the diagonal block's coefficients read behind the neighbour's
-// product.  The arithmetic is the same, and so is each column's result.
-template <int RC, bool WIDE>
+template <int RC>
+struct SvFwdSmem {
+  alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block over its pivots, and L_{b,b-1}
+  double Ls1[SV_NB][SV_TS];
+  double part[SV_NB][RC + 1];            // the fold's sums
+  double near[RC][SV_NB];                // L_{b,b-2} y_{b-2}
+  double rhs[RC][SV_NB];                 // the block's entries of B
+  double rdiag[SV_NB];
+};
+template <int RC>
 __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int64_t lda, int64_t n,
                                                const double* __restrict__ B, int64_t nc, int64_t ldb, double* Ypay,
                                                double* __restrict__ Xpay, SvWs* ws, int64_t wait_ticks, int32_t npass,
                                                int64_t pstride, int32_t g) {
   static_assert(RC >= 1 && RC <= SV_THREADS / 64, "one chain wave per right-hand side");
-  __shared__ double part[SV_NB][RC + 1];
-  __shared__ alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block, L_{b,b-1} and L_{b,b-2}, rows of lanes
-  __shared__ alignas(16) double Ls1[SV_NB][SV_TS];
-  __shared__ alignas(16) double Ls2[WIDE ? SV_NB : 1][SV_TS];  // (in registers, later, when not WIDE)
-  __shared__ double rdiag[SV_NB];
+  __shared__ SvFwdSmem<RC> sm;
+  auto& part = sm.part;
+  auto& near = sm.near;
+  auto& Lbb = sm.Lbb;
+  auto& Ls1 = sm.Ls1;
+  auto& rdiag = sm.rdiag;
   const int tid = threadIdx.x;
   const int32_t b = g / npass, pass = g - b * npass;
   B += pass * RC;
@@ -510,29 +593,35 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
   Xpay += pass * pstride;
   const int64_t r0 = (int64_t)b * SV_NB;
   const int nr = n - r0 < SV_NB ? (int)(n - r0) : SV_NB;
-  const int w = tid >> 6, lane = tid & 63, rr = lane >> 4, q = lane & 15;
+  int w = tid >> 6, lane = tid & 63, rr = lane >> 4, q = lane & 15;
   // the backward sweep's payload of this block starts as the sentinel
   for (int e = tid; e < SV_NB * RC; e += SV_THREADS)
     Xpay[(int64_t)b * SV_NB * RC + e] = __builtin_bit_cast(double, SV_SENTINEL);
   // a payload column with no right-hand side is published as zero at once
   if (w >= nc && w < RC) sv_pay_st(Ypay + ((int64_t)b * SV_NB + lane) * RC + w, 0.0);
-  // the chain wave's own entries of B, read before any wait
-  const double bown = (w < nc && lane < nr) ? B[(r0 + lane) * ldb + w] : 0.0;
-  // staged before any wait: the diagonal block, L_{b,b-1} and L_{b,b-2}
+  // the chain wave's own entries of B, read before any wait (kept in LDS, as
+  // the fold takes every register)
+  if (w < nc) sm.rhs[w][lane] = lane < nr ? B[(r0 + lane) * ldb + w] : 0.0;
+  // before any wait: the diagonal block and L_{b,b-1} to LDS, and the lane's
+  // coefficients of L_{b,b-2} (rows past n read its last row; dropped below)
+  double l2[16];
   {
-    double td[16], t1[16], t2[16];
+    double td[16], t1[16];
     sv_tile_load(L, lda, n, r0, r0, td);
     if (b > 0) sv_tile_load(L, lda, n, r0, r0 - SV_NB, t1);
-    if (WIDE && b > 1) sv_tile_load(L, lda, n, r0, r0 - 2 * SV_NB, t2);
-    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[i][k] = v; });
+    if (b > 1) {
+      const int64_t R = r0 + 16 * w + q;
+      const double* p = L + (R < n ? R : n - 1) * lda + r0 - 2 * SV_NB + rr;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int i = w + 4 * e;
-      if (b > 0) Ls1[i][lane] = i < nr ? t1[e] : 0.0;
-      if constexpr (WIDE) {
-        if (b > 1) Ls2[i][lane] = i < nr ? t2[e] : 0.0;
-      }
+      for (int m = 0; m < 16; ++m) l2[m] = p[4 * m];
     }
+    sv_rdiag_put(td, nr, rdiag);
+    if (b > 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) Ls1[w + 4 * e][lane] = w + 4 * e < nr ? t1[e] : 0.0;
+    }
+    __syncthreads();
+    sv_lower_put(td, nr, [&](int i, int k, double v) { Lbb[i][k] = v * rdiag[i]; });
   }
   int frow[4];
 #pragma unroll
@@ -542,11 +631,16 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
   // selects them away after the loads (a block-uniform choice between the
   // two, so no load sits in a branch of its own).
   const bool full = r0 + SV_NB <= n;
+  // (32-bit offsets from the block's first row: a register a row, not two)
+  unsigned fo[4];
+#pragma unroll
+  for (int s2 = 0; s2 < 4; ++s2)
+    fo[s2] = (unsigned)(8 * ((frow[s2] < nr ? frow[s2] : nr - 1) * lda + q));
   auto lload = [&](int32_t j, double (*dst)[4]) {
+    const char* const base = (const char*)(L + r0 * lda + (int64_t)j * SV_NB);
 #pragma unroll
     for (int s2 = 0; s2 < 4; ++s2) {
-      const int64_t R = r0 + frow[s2];
-      const double* p = L + (full || R < n ? R : n - 1) * lda + q + (int64_t)j * SV_NB;
+      const double* p = (const double*)(base + fo[s2]);
 #pragma unroll
       for (int m = 0; m < 4; ++m) dst[s2][m] = p[16 * m];
     }
@@ -557,11 +651,13 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
         for (int m = 0; m < 4; ++m) dst[s2][m] = r0 + frow[s2] < n ? dst[s2][m] : 0.0;
     }
   };
+  const unsigned yo = (unsigned)(8 * RC * q);
   auto yload = [&](int32_t j, double (*y)[RC]) {
+    const char* const base = (const char*)(Ypay + (int64_t)j * SV_NB * RC);
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int c = 0; c < RC; ++c) y[m][c] = sv_pay_ld(Ypay + ((int64_t)j * SV_NB + 16 * m + q) * RC + c);
+      for (int c = 0; c < RC; ++c) y[m][c] = sv_pay_ld((const double*)(base + yo) + 16 * m * RC + c);
   };
   const int32_t nfold = b > 2 ? b - 2 : 0;  // blocks 0 .. b - 3
   double acc[4][RC];
@@ -569,14 +665,12 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
   for (int s2 = 0; s2 < 4; ++s2)
 #pragma unroll
     for (int c = 0; c < RC; ++c) acc[s2][c] = 0.0;
-  // the last folded tile (block b - 3) is read before any wait
-  double lt[4][4], lc[4][4], ya[4][RC];
+  double lc[4][4], ya[4][RC];
   bool ok = true;
   if (nfold > 0) {
-    lload(nfold - 1, lt);
+    lload(0, lc);
     yload(0, ya);
   }
-  if (nfold > 1) lload(0, lc);
   auto pending = [&] {
     bool p = false;
 #pragma unroll
@@ -603,25 +697,29 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
       break;
     }
     if (j + 1 == nfold) {
-      fold(lt);
+      fold(lc);
       break;
     }
-    // the next block, while this one is folded (its tile unless it is the last)
-    const bool more = j + 2 < nfold;
+    // the next block, while this one is folded
     double ln[4][4], yn[4][RC];
-    if (more) lload(j + 1, ln);
+    lload(j + 1, ln);
     yload(j + 1, yn);
     fold(lc);
-    if (more) {
 #pragma unroll
-      for (int s2 = 0; s2 < 4; ++s2)
+    for (int m = 0; m < 4; ++m) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) lc[s2][m] = ln[s2][m];
-    }
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
+      for (int s2 = 0; s2 < 4; ++s2) lc[s2][m] = ln[s2][m];
 #pragma unroll
       for (int c = 0; c < RC; ++c) ya[m][c] = yn[m][c];
+    }
+  }
+  {  // the lane's place anew, so that it takes no registers during the fold
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    w = t >> 6;
+    lane = t & 63;
+    rr = lane >> 4;
+    q = lane & 15;
   }
   // butterfly over the 16 lanes of each row, then one lane writes the sum
 #pragma unroll
@@ -631,55 +729,47 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
       double v = acc[s2][c];
 #pragma unroll
       for (int k = 1; k < 16; k <<= 1) v += __shfl_xor(v, k, 16);
-      if (q == 0) part[frow[s2]][c] = v;
+      if (q == 0) part[16 * s2 + 4 * w + rr][c] = v;
     }
+  // from here on the chain: this workgroup's waves first in issue on their
+  // SIMDs (the other workgroup on the CU streams its fold meanwhile)
+  __builtin_amdgcn_s_setprio(3);
+  double l1[SV_NB];  // row `lane` of L_{b,b-1}
+  if (w < nc && b > 0) {
+    sv_coefs<0, SV_NB>(Ls1, lane, l1);
+    sv_pin<0, SV_NB>(l1);
+  }
+  if (ok && b > 1)
+    ok = sv_near_product<RC>(Ypay + (int64_t)(b - 2) * SV_NB * RC, l2, near, w, rr, q, ws, wait_ticks);
   const bool all_ok = __syncthreads_and(ok);
   if (w < nc) {
-    // the chain wave goes first in issue on its SIMD (the other workgroup on
-    // the CU streams its fold meanwhile)
-    __builtin_amdgcn_s_setprio(3);
     const int c = w;
-    double v = bown - (lane < nr ? part[lane][c] : 0.0);
-    double y[4], l1[SV_NB], lr[SV_NB];
+    double v = sm.rhs[c][lane] - (lane < nr ? part[lane][c] : 0.0);
+    if (b > 1) v = v - near[c][lane];
+    double y[4], lr[SV_NB];
     const double rl = rdiag[lane];
     bool got = all_ok;
-    if (got && b > 1) {
-      if constexpr (WIDE) {
-        sv_coefs(Ls2, lane, l1);
-      } else {  // row `lane` of L_{b,b-2} from memory (32 lines of it per wave stay in L1)
-        const double* p = L + (r0 + (lane < nr ? lane : nr - 1)) * lda + r0 - 2 * SV_NB;
-        sv_row_ld(p, l1);
-      }
-      sv_pin(l1);
-      got = sv_wait_col<RC, WIDE, false>(Ypay + (int64_t)(b - 2) * SV_NB * RC + c, y, lane, ws, wait_ticks);
-      if (got) v = v - sv_dot64(l1, y);
-    }
-    // row `lane` of L_{b,b-1} (and, WIDE, of L_bb scaled by the reciprocal of
-    // its pivot) into registers before the wait for the neighbour
-    if constexpr (WIDE) {
-      sv_coefs(Lbb, lane, rl, lr);
-      sv_pin(lr);
-    }
+    // the first half of row `lane` of the diagonal block in front of the
+    // wait, the second behind the product, as registers come free
+    sv_coefs<0, 32>(Lbb, lane, lr);
+    sv_pin<0, 32>(lr);
     if (got && b > 0) {
-      sv_coefs(Ls1, lane, l1);
-      sv_pin(l1);
-      got = sv_wait_col<RC, WIDE, true>(Ypay + (int64_t)(b - 1) * SV_NB * RC + c, y, lane, ws, wait_ticks);
+      got = sv_wait_col<RC>(Ypay + (int64_t)(b - 1) * SV_NB * RC + c, y, lane, ws, wait_ticks);
       if (got) v = v - sv_dot64(l1, y);
     }
-    if constexpr (!WIDE) sv_coefs(Lbb, lane, rl, lr);
     if (lane >= nr) v = 0.0;
-    v = sv_chain64_fwd(v * rl, lr);
+    v = sv_chain64_fwd(v * rl, lr, [&](auto h) { sv_coefs<32 + 16 * h, 48 + 16 * h>(Lbb, lane, lr); });
     if (got) sv_pay_st(Ypay + ((int64_t)b * SV_NB + lane) * RC + c, lane < nr ? v : 0.0);
-    __builtin_amdgcn_s_setprio(0);
   }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 // --------------------------------------------------------------- backward
 // x_b = L_bb^{-T} (y_b - sum_{j>b} L_jb^T x_j), one block per workgroup:
-// the four waves fold the blocks j >= b + 3 as their payloads arrive, then
-// wave c takes right-hand side c alone: it subtracts the fold, waits for
-// x_{b+2} and subtracts L_{b+2,b}^T x_{b+2}, waits for x_{b+1} and subtracts
-// L_{b+1,b}^T x_{b+1}, substitutes, writes B and publishes its column.
+// the four waves fold the blocks j >= b + 3 as their payloads arrive and form
+// L_{b+2,b}^T x_{b+2}, then wave c takes right-hand side c alone: it waits for
+// x_{b+1}, subtracts L_{b+1,b}^T x_{b+1}, substitutes, writes B and publishes
+// its column (registers and LDS as in the forward sweep).
 // Fold layout: thread (r, p) covers output row r of the block (column r of
 // each L_jb) and rows 16 p .. 16 p + 15 of every folded block; consecutive
 // r are consecutive addresses, so each wave reads 64 contiguous doubles per
@@ -689,17 +779,26 @@ __device__ __forceinline__ void sv_forward_run(const double* __restrict__ L, int
 // (d0 + d1) + (d2 + d3); then the substitution (sv_chain64_bwd).
 // The workgroup with ticket g of the backward sweep (passes interleaved in
 // ticket order, as in the forward sweep).
-template <int RC, bool WIDE>
+template <int RC>
+struct SvBwdSmem {
+  alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block over its pivots and L_{b+1,b}, transposed
+  double Ls1[SV_NB][SV_TS];
+  double part[4][SV_NB][RC + 1];         // the fold's quarters
+  double near[RC][SV_NB];                // L_{b+2,b}^T x_{b+2}
+  double rdiag[SV_NB];
+};
+template <int RC>
 __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, int64_t lda, int64_t n,
                                                 double* __restrict__ B, int64_t nc, int64_t ldb,
                                                 const double* __restrict__ Ypay, double* Xpay, SvWs* ws,
                                                 int64_t wait_ticks, int32_t npass, int64_t pstride, int32_t g) {
   static_assert(RC >= 1 && RC <= SV_THREADS / 64, "one chain wave per right-hand side");
-  __shared__ double part[4][SV_NB][RC + 1];
-  __shared__ alignas(16) double Lbb[SV_NB][SV_TS];  // the diagonal block, L_{b+1,b} and L_{b+2,b}, transposed:
-  __shared__ alignas(16) double Ls1[SV_NB][SV_TS];  // rows of lanes
-  __shared__ alignas(16) double Ls2[WIDE ? SV_NB : 1][SV_TS];  // (in registers, later, when not WIDE)
-  __shared__ double rdiag[SV_NB];
+  __shared__ SvBwdSmem<RC> sm;
+  auto& part = sm.part;
+  auto& near = sm.near;
+  auto& Lbb = sm.Lbb;
+  auto& Ls1 = sm.Ls1;
+  auto& rdiag = sm.rdiag;
   const int tid = threadIdx.x;
   const int32_t nb = (int32_t)((n + SV_NB - 1) / SV_NB);
   const int32_t t = g / npass, pass = g - t * npass;
@@ -715,21 +814,29 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
   // the chain wave's own entries of y (published by the forward sweep, an
   // earlier launch)
   const double yown = w < nc ? Ypay[((int64_t)b * SV_NB + lane) * RC + w] : 0.0;
+  const int rr = lane >> 4, q16 = lane & 15;
+  double l2[16];  // the lane's coefficients of L_{b+2,b} (where there is one, block b is full)
   {
     const int64_t j1 = r0 + SV_NB, j2 = r0 + 2 * SV_NB;
-    double td[16], t1[16], t2[16];
+    double td[16], t1[16];
     sv_tile_load(L, lda, n, r0, r0, td);
     if (b + 1 < nb) sv_tile_load(L, lda, n, j1, r0, t1);
-    if (WIDE && b + 2 < nb) sv_tile_load(L, lda, n, j2, r0, t2);
-    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[k][i] = v; });
+    if (b + 2 < nb) {
+      const double* pl = L + r0 + 16 * w + q16;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int k = p + 4 * e;
-      if (b + 1 < nb) Ls1[r][k] = j1 + k < n ? t1[e] : 0.0;
-      if constexpr (WIDE) {
-        if (b + 2 < nb) Ls2[r][k] = j2 + k < n ? t2[e] : 0.0;
+      for (int m = 0; m < 16; ++m) {
+        const int64_t R = j2 + 4 * m + rr;
+        l2[m] = pl[(R < n ? R : n - 1) * lda];
+        l2[m] = R < n ? l2[m] : 0.0;
       }
     }
+    sv_rdiag_put(td, nr, rdiag);
+    if (b + 1 < nb) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) Ls1[r][p + 4 * e] = j1 + p + 4 * e < n ? t1[e] : 0.0;
+    }
+    __syncthreads();
+    sv_lower_put(td, nr, [&](int i, int k, double v) { Lbb[k][i] = v * rdiag[k]; });
   }
   // Only the blocks b <= nb - 4 fold, and they are full, so the column
   // r0 + r is inside the matrix.  A full block j is read with 16 plain
@@ -762,14 +869,12 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
   double acc[RC];
 #pragma unroll
   for (int c = 0; c < RC; ++c) acc[c] = 0.0;
-  // the last folded tile (block b + 3) is read before any wait
-  double lt[16], lc[16], xa = 0.0;
+  double lc[16], xa = 0.0;
   bool ok = true;
   if (jlast < nb) {
-    load_col(jlast, lt);
+    load_col(nb - 1, lc);
     xa = xload(nb - 1);
   }
-  if (jlast < nb - 1) load_col(nb - 1, lc);
   // the probe: the last of this quarter's rows, column 0
   auto probe = [&](int32_t j) { return Xpay + ((int64_t)j * SV_NB + 16 * p + 15) * RC; };
   auto fold = [&](const double* l) {
@@ -785,86 +890,74 @@ __device__ __forceinline__ void sv_backward_run(const double* __restrict__ L, in
       break;
     }
     if (j == jlast) {
-      fold(lt);
+      fold(lc);
       break;
     }
-    // the next block, while this one is folded (its tile unless it is the last)
-    const bool more = j - 1 > jlast;
+    // the next block, while this one is folded
     double ln[16];
-    if (more) load_col(j - 1, ln);
+    load_col(j - 1, ln);
     const double xn = xload(j - 1);
     fold(lc);
-    if (more) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) lc[k] = ln[k];
-    }
+    for (int k = 0; k < 16; ++k) lc[k] = ln[k];
     xa = xn;
   }
 #pragma unroll
   for (int c = 0; c < RC; ++c) part[p][r][c] = acc[c];
+  __builtin_amdgcn_s_setprio(3);  // the chain first in issue (as in the forward sweep)
+  double l1[SV_NB];  // column `lane` of L_{b+1,b}
+  if (w < nc && b + 1 < nb) {
+    sv_coefs<0, SV_NB>(Ls1, lane, l1);
+    sv_pin<0, SV_NB>(l1);
+  }
+  if (ok && b + 2 < nb)
+    ok = sv_near_product<RC>(Xpay + (int64_t)(b + 2) * SV_NB * RC, l2, near, w, rr, q16, ws, wait_ticks);
   const bool all_ok = __syncthreads_and(ok);
   if (w < nc) {
-    __builtin_amdgcn_s_setprio(3);  // the chain wave first in issue (as in the forward sweep)
     const int c = w;
-    const double sm = ((part[0][lane][c] + part[1][lane][c]) + part[2][lane][c]) + part[3][lane][c];
-    double v = lane < nr ? yown - sm : 0.0;
-    double x[4], l1[SV_NB], lc2[SV_NB];
+    const double sum = ((part[0][lane][c] + part[1][lane][c]) + part[2][lane][c]) + part[3][lane][c];
+    double v = lane < nr ? yown - sum : 0.0;
+    if (b + 2 < nb) v = v - near[c][lane];
+    double x[4], lc2[SV_NB];
     const double rl = rdiag[lane];
     bool got = all_ok;
-    if (got && b + 2 < nb) {
-      if constexpr (WIDE) {
-        sv_coefs(Ls2, lane, l1);
-      } else {  // column `lane` of L_{b+2,b} from memory (rows past n: their x is zero)
-        const int64_t j2 = r0 + 2 * SV_NB;
-#pragma unroll
-        for (int k = 0; k < SV_NB; ++k) l1[k] = L[(j2 + k < n ? j2 + k : n - 1) * lda + r0 + lane];
-      }
-      sv_pin(l1);
-      got = sv_wait_col<RC, WIDE, false>(Xpay + (int64_t)(b + 2) * SV_NB * RC + c, x, lane, ws, wait_ticks);
-      if (got) v = v - sv_dot64(l1, x);
-    }
-    // column `lane` of L_{b+1,b} (and, WIDE, of L_bb scaled by the reciprocal
-    // of its pivot) into registers before the wait for the neighbour
-    if constexpr (WIDE) {
-      sv_coefs(Lbb, lane, rl, lc2);
-      sv_pin(lc2);
-    }
+    // column `lane` of the diagonal block in two halves, as in the forward
+    // sweep; this chain starts with the second
+    sv_coefs<32, SV_NB>(Lbb, lane, lc2);
+    sv_pin<32, SV_NB>(lc2);
     if (got && b + 1 < nb) {
-      sv_coefs(Ls1, lane, l1);
-      sv_pin(l1);
-      got = sv_wait_col<RC, WIDE, true>(Xpay + (int64_t)(b + 1) * SV_NB * RC + c, x, lane, ws, wait_ticks);
+      got = sv_wait_col<RC>(Xpay + (int64_t)(b + 1) * SV_NB * RC + c, x, lane, ws, wait_ticks);
       if (got) v = v - sv_dot64(l1, x);
     }
-    if constexpr (!WIDE) sv_coefs(Lbb, lane, rl, lc2);
     if (lane >= nr) v = 0.0;
-    v = sv_chain64_bwd(v * rl, lc2);
+    v = sv_chain64_bwd(v * rl, lc2, [&](auto h) { sv_coefs<16 - 16 * h, 32 - 16 * h>(Lbb, lane, lc2); });
     if (lane < nr) B[(r0 + lane) * ldb + c] = v;
     if (got) sv_pay_st(Xpay + ((int64_t)b * SV_NB + lane) * RC + c, lane < nr ? v : 0.0);
-    __builtin_amdgcn_s_setprio(0);
   }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 // One solve per launch pair: the ticket from the solve's own counters.
-template <int RC, bool WIDE>
-__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_forward(const double* __restrict__ L, int64_t lda, int64_t n,
+template <int RC>
+__global__ __launch_bounds__(SV_THREADS, 2) void sv_forward(const double* __restrict__ L, int64_t lda, int64_t n,
                                                          const double* __restrict__ B, int64_t nc, int64_t ldb,
                                                          double* Ypay, double* __restrict__ Xpay, SvWs* ws,
                                                          int64_t wait_ticks, int32_t npass, int64_t pstride) {
   __shared__ int32_t s_g;
   if (threadIdx.x == 0) s_g = __hip_atomic_fetch_add(&ws->ticket_f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  sv_forward_run<RC, WIDE>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
+  sv_forward_run<RC>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
 }
 
-template <int RC, bool WIDE>
-__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_backward(const double* __restrict__ L, int64_t lda, int64_t n,
+template <int RC>
+__global__ __launch_bounds__(SV_THREADS, 2) void sv_backward(const double* __restrict__ L, int64_t lda, int64_t n,
                                                           double* __restrict__ B, int64_t nc, int64_t ldb,
                                                           const double* __restrict__ Ypay, double* Xpay, SvWs* ws,
                                                           int64_t wait_ticks, int32_t npass, int64_t pstride) {
   __shared__ int32_t s_g;
   if (threadIdx.x == 0) s_g = __hip_atomic_fetch_add(&ws->ticket_b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  sv_backward_run<RC, WIDE>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
+  sv_backward_run<RC>(L, lda, n, B, nc, ldb, Ypay, Xpay, ws, wait_ticks, npass, pstride, sv_uniform(s_g));
 }
 
 // ------------------------------------------------- several solves per launch
@@ -897,8 +990,7 @@ __device__ __forceinline__ void sv_take_job(const TcSolveJob* jobs, int64_t coun
   g = sv_uniform((int32_t)(t - jobs[job].first));
 }
 
-template <bool WIDE>
-__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_forward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
+__global__ __launch_bounds__(SV_THREADS, 2) void sv_forward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
                                                               int64_t wait_ticks) {
   int32_t j, g;
   sv_take_job(jobs, count, ctr, j, g);
@@ -910,12 +1002,11 @@ __global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_forward_many(cons
   SvWs* ws = (SvWs*)work;
   double* ypay = (double*)(work + sv_jr256(sizeof(SvWs)));
   double* xpay = (double*)((char*)ypay + sv_jr256(8 * stride * np));
-  sv_forward_run<SV_RC_MID, WIDE>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
+  sv_forward_run<SV_RC_MID>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
                             (int32_t)np, stride, g);
 }
 
-template <bool WIDE>
-__global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_backward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
+__global__ __launch_bounds__(SV_THREADS, 2) void sv_backward_many(const TcSolveJob* jobs, int64_t count, int32_t* ctr,
                                                                int64_t wait_ticks) {
   int32_t j, g;
   sv_take_job(jobs, count, ctr + 1, j, g);
@@ -925,7 +1016,7 @@ __global__ __launch_bounds__(SV_THREADS, WIDE ? 1 : 2) void sv_backward_many(con
   SvWs* ws = (SvWs*)work;
   const double* ypay = (const double*)(work + sv_jr256(sizeof(SvWs)));
   double* xpay = (double*)((char*)ypay + sv_jr256(8 * stride * np));
-  sv_backward_run<SV_RC_MID, WIDE>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
+  sv_backward_run<SV_RC_MID>(tc_global(J.L), J.lda, J.n, tc_global(J.B), J.nrhs, J.ldb, ypay, xpay, ws, wait_ticks,
                              (int32_t)np, stride, g);
 }
 
@@ -990,7 +1081,8 @@ __global__ __launch_bounds__(SV_THREADS) void sv_invert_diag(const double* __res
   {
     double td[16];
     sv_tile_load(L, lda, n, r0, r0, td);
-    sv_diag_put(td, nr, rdiag, [&](int i, int k, double v) { Lbb[i][k] = v; });
+    sv_rdiag_put(td, nr, rdiag);
+    sv_lower_put(td, nr, [&](int i, int k, double v) { Lbb[i][k] = v; });
   }
   __syncthreads();
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1471,14 +1563,27 @@ void sv_launch_fill(const SvMap& m, hipStream_t st, int words = SV_COUNTER_WORDS
 }
 }  // namespace
 
-// Which form of the sweeps a launch of `blocks` workgroups takes: up to four
-// per CU the chain's latency sets the time, beyond that the folds' share of
-// the chip.  Measured, WIDE and not (us; before: 2.4 us a block step where
-// WIDE takes 1.6): n=1500, 1 column: 97, 96 (127 before); n=8192, 16 columns,
-// 512 workgroups: 771, 990 (950); n=16384, 16 columns, 1024: 2160, 2205
-// (2155); n=32768, 8 columns, 1024: 4420, 4620 (4580); n=8192, 64 columns,
-// 2048: 1780, 1495 (1460); n=32768, 64 columns, 8192: 25100, 17650 (17500).
-static bool sv_wide(int64_t blocks) { return blocks <= 1024; }
+// A launch of between 7/4 and two blocks per CU asks for so much LDS that a CU
+// takes one of its workgroups at a time (beside one of a factorization's
+// kernels, at most 78.4 KB).  All its blocks would be resident in pairs, and
+// every step of the chain would share its CU with another block's fold; with
+// fewer blocks many CUs hold one anyway, and with more the folds' share of the
+// chip sets the time.  Measured, one a CU against two (us): n=32768, 1 column
+// (512 blocks) 2137, 2395; n=30000 (469) 2070, 2137; n=28000 (438) 1944, 1967,
+// 4 columns 2828, 2760; n=8192, 16 columns (512) 734, 776; 12 (384) 802, 724;
+// 20 (640) 920, 828; n=16384, 16 columns (1024) 2068, 1909.
+#define SV_ALONE_LDS 83200
+static unsigned sv_pad(int64_t blocks, size_t used) {
+  static std::atomic<int> cached[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  int cus = cached[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cached[dev].store(cus, std::memory_order_relaxed);
+  }
+  return 4 * blocks > 7 * (int64_t)cus && blocks <= 2 * (int64_t)cus ? (unsigned)(SV_ALONE_LDS - used) : 0;
+}
 
 int64_t tc_solve_ws_bytes(int64_t n, int64_t nrhs, bool inv) {
   return sv_r256(sizeof(SvWs)) + 2 * sv_r256(8 * sv_pay_entries(n, sv_pay_width(nrhs, inv)) * sv_npass(nrhs, inv));
@@ -1541,11 +1646,10 @@ int tc_launch_solve_many(const TcSolveJob* jobs, int64_t count, int64_t tickets,
   bx = bx < 1 ? 1 : (bx > 64 ? 64 : bx);
   const int64_t by = count < 65535 ? count : 65535;
   hipLaunchKernelGGL(sv_fill_many, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, st, jobs, count, ctr);
-  const bool wide = sv_wide(tickets);
-  hipLaunchKernelGGL(wide ? sv_forward_many<true> : sv_forward_many<false>, dim3((unsigned)tickets), dim3(SV_THREADS),
-                     0, st, jobs, count, ctr, wait_ticks);
-  hipLaunchKernelGGL(wide ? sv_backward_many<true> : sv_backward_many<false>, dim3((unsigned)tickets),
-                     dim3(SV_THREADS), 0, st, jobs, count, ctr, wait_ticks);
+  hipLaunchKernelGGL(sv_forward_many, dim3((unsigned)tickets), dim3(SV_THREADS),
+                     sv_pad(tickets, sizeof(SvFwdSmem<SV_RC_MID>)), st, jobs, count, ctr, wait_ticks);
+  hipLaunchKernelGGL(sv_backward_many, dim3((unsigned)tickets), dim3(SV_THREADS),
+                     sv_pad(tickets, sizeof(SvBwdSmem<SV_RC_MID>)), st, jobs, count, ctr, wait_ticks);
   return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;
 }
 
@@ -1557,11 +1661,12 @@ int tc_launch_solve(const double* L, int64_t n, int64_t lda, int64_t T, double* 
   if (nrhs <= SV_RC_SMALL) {  // measured faster for one or two right-hand sides
     const SvMap m = sv_map(work, n, SV_RC_SMALL);
     sv_launch_fill(m, st, sizeof(SvWs) / 4);  // the status too
-    const bool wide = sv_wide(nb);
-    hipLaunchKernelGGL((wide ? sv_forward<SV_RC_SMALL, true> : sv_forward<SV_RC_SMALL, false>), dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n,
-                       (const double*)B, nrhs, ldb, m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
-    hipLaunchKernelGGL((wide ? sv_backward<SV_RC_SMALL, true> : sv_backward<SV_RC_SMALL, false>), dim3((unsigned)nb), dim3(SV_THREADS), 0, st, L, lda, n, B, nrhs,
-                       ldb, (const double*)m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
+    hipLaunchKernelGGL(sv_forward<SV_RC_SMALL>, dim3((unsigned)nb), dim3(SV_THREADS),
+                       sv_pad(nb, sizeof(SvFwdSmem<SV_RC_SMALL>)), st, L, lda, n, (const double*)B, nrhs, ldb,
+                       m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
+    hipLaunchKernelGGL(sv_backward<SV_RC_SMALL>, dim3((unsigned)nb), dim3(SV_THREADS),
+                       sv_pad(nb, sizeof(SvBwdSmem<SV_RC_SMALL>)), st, L, lda, n, B, nrhs, ldb,
+                       (const double*)m.ypay, m.xpay, ws, wait_ticks, 1, m.stride);
     return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;
   }
   // one chain per wave, up to SV_PASSES passes of four in one launch pair
@@ -1575,11 +1680,12 @@ int tc_launch_solve(const double* L, int64_t n, int64_t lda, int64_t T, double* 
     const int64_t np = (nc + SV_RC_MID - 1) / SV_RC_MID;
     // the first launch pair clears the call's status, later ones keep it
     sv_launch_fill(m, st, c0 == 0 ? (int)(sizeof(SvWs) / 4) : SV_COUNTER_WORDS);
-    const bool wide = sv_wide(nb * np);
-    hipLaunchKernelGGL((wide ? sv_forward<SV_RC_MID, true> : sv_forward<SV_RC_MID, false>), dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
-                       (const double*)(B + c0), nc, ldb, m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
-    hipLaunchKernelGGL((wide ? sv_backward<SV_RC_MID, true> : sv_backward<SV_RC_MID, false>), dim3((unsigned)(nb * np)), dim3(SV_THREADS), 0, st, L, lda, n,
-                       B + c0, nc, ldb, (const double*)m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
+    hipLaunchKernelGGL(sv_forward<SV_RC_MID>, dim3((unsigned)(nb * np)), dim3(SV_THREADS),
+                       sv_pad(nb * np, sizeof(SvFwdSmem<SV_RC_MID>)), st, L, lda, n, (const double*)(B + c0), nc, ldb,
+                       m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
+    hipLaunchKernelGGL(sv_backward<SV_RC_MID>, dim3((unsigned)(nb * np)), dim3(SV_THREADS),
+                       sv_pad(nb * np, sizeof(SvBwdSmem<SV_RC_MID>)), st, L, lda, n, B + c0, nc, ldb,
+                       (const double*)m.ypay, m.xpay, ws, wait_ticks, (int32_t)np, m.stride);
   }
   return hipGetLastError() == hipSuccess ? 0 : TC_LAUNCH_EDEVICE;
 }

@@ -8,14 +8,12 @@ tc_sync, whose every result is read by later units, hold no other global
 store, and the bodies that both kinds of schedule use do not compile without
 the caller's choice.
 """
-import os
 import re
-import shutil
 import subprocess
 
 import pytest
 
-from paper_2606_11937_amd import build
+import device_listing
 
 BODIES = """
 #include "tile_ops.h"
@@ -29,21 +27,13 @@ __global__ void k(double* C, const double* P, const float* Q, int64_t lda) {
 
 @pytest.fixture(scope="module")
 def hipcc():
-    if shutil.which("hipcc") is None:
-        pytest.skip("no hipcc")
-    build.gen_tuned_tiles()
-    return ["hipcc", *build.HIPFLAGS, "-I", build.GEN_DIR, "-I", build.CSRC, "-x", "hip"]
+    return device_listing.hipcc()
 
 
-def test_persistent_kernels_store_at_device_scope(hipcc, tmp_path):
-    out = tmp_path / "k.s"
-    subprocess.run([*hipcc, "-S", "--cuda-device-only", os.path.join(build.CSRC, "kernels.hip"), "-o", str(out)],
-                   check=True, capture_output=True)
-    lines = out.read_text().splitlines()
+def test_persistent_kernels_store_at_device_scope():
     for kernel in ("tc_async", "tc_sync"):
-        start = next(i for i, l in enumerate(lines) if re.match(r"_Z\d+%s[A-Z].*:" % kernel, l))
-        end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
-        stores = [l.strip() for l in lines[start:end] if re.match(r"\s+(global|flat|buffer)_store", l)]
+        lines = device_listing.kernel_body("kernels.hip", kernel)
+        stores = [l.strip() for l in lines if re.match(r"\s+(global|flat|buffer)_store", l)]
         assert len(stores) > 50
         assert [s for s in stores if not re.search(r"\bsc1\b", s)] == []
 
