@@ -1058,12 +1058,13 @@ __device__ __forceinline__ void tc_pk_store_col(double* __restrict__ D, int64_t 
 // Pivot J of the diagonal block held one row per lane (the same in every
 // 16-lane row of the wave), and the trailing update a_ik -= l_ij l_kj.  The
 // square root and its reciprocal come from one hardware estimate of
-// 1 / sqrt(d) (5e-8): a third-order step for the reciprocal root, then one
-// residual correction each for the root and for 1 / root.  In the range the
-// caller checks, root and reciprocal are the bits of sqrt(d) and 1 / sqrt(d)
-// (4M random values in [1, 4) and all squares up to 60000^2; 426 roots
-// differed in 4M over the whole exponent range, below 2^-767), in 70 cycles
-// of one wave against about 150 for the two library sequences.  m collects
+// 1 / sqrt(d) (5e-8): a third-order step for the reciprocal root (the binomial
+// series of (1 - e)^(-1/2) to e^2), then one residual correction each for the
+// root and for 1 / root (Markstein's method).  In the range the caller checks,
+// root and reciprocal are the bits of sqrt(d) and of 1 / sqrt(d): 420,000
+// pivots are compared in tests/test_gpu_pivot_root.py (two octaves, all
+// squares up to 60000^2, their neighbours, exponents 2^-698 .. 2^1000).  70
+// cycles of one wave against about 150 for the two library sequences.  m collects
 // the smallest high word of a pivot; a pivot of zero, infinity or NaN turns
 // every later one of the block into NaN.
 #define TC_PIV_LO ((1023 - 700) << 20)  // 2^-700
