@@ -85,16 +85,10 @@ __device__ __forceinline__ void tc_st2(double* p, double x, double y) {
   }
 }
 
-// Four consecutive doubles of one row, as two 16-byte loads.
+// Four consecutive doubles of one row.
 struct tc_q4 {
   tc_d2 lo, hi;
 };
-__device__ __forceinline__ tc_q4 tc_ld4(const double* p) {
-  tc_q4 q;
-  q.lo = *(const tc_d2*)p;
-  q.hi = *(const tc_d2*)(p + 2);
-  return q;
-}
 __device__ __forceinline__ double tc_el(const tc_q4& q, int m) {
   return m == 0 ? q.lo.x : m == 1 ? q.lo.y : m == 2 ? q.hi.x : q.hi.y;
 }
