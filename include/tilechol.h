@@ -18,9 +18,11 @@
  * Conventions shared by every entry point
  *   Storage   row-major: element (i, j) of A lives at A[i * lda + j],
  *             lda >= max(1, n).  Only the lower triangle including the
- *             diagonal is read or written; the strict upper triangle is
- *             never touched.  (A column-major caller holding a symmetric A
- *             finds L^T in its upper triangle.)
+ *             diagonal is used and written.  The strict upper triangle is
+ *             never written and no result depends on its contents (any bits,
+ *             NaN too), but blocks that meet the diagonal are read whole, so
+ *             it has to be readable memory.  (A column-major caller holding a
+ *             symmetric A finds L^T in its upper triangle.)
  *   Tiles     M = ceil(n / T) tiles per dimension; the last tile row and
  *             column are ragged with side n - (M - 1) T.  T > n is allowed
  *             (one tile).  All sizes and offsets are 64-bit; n and lda are

@@ -4,7 +4,9 @@
 //
 // Every body runs on one workgroup of TC_THREADS = 256 threads (4 wave64s).
 // Matrices are row-major with leading dimension lda; only lower-triangle
-// entries are read or written.
+// entries are written.  Blocks on the diagonal are read in whole pairs and
+// rows, and what lies above the diagonal is dropped or feeds nothing on or
+// below it.
 //
 // The contraction core is v_mfma_f64_16x16x4_f64 (FP64 matrix cores).  Its
 // operand/result lane layout, measured on gfx950 with one-hot inputs:
