@@ -73,11 +73,11 @@ TRAFFIC = {
     # (schedule, n, T): (bytes per launch of the roofline kernel, sha256 of the
     # kernel sources); the profiles under profiles/ hold the counter readings
     # (forkjoin_n32768_T1024_kernels.md, lookahead_n32768_T1024_kernels.md)
-    ("fork_join", 32768, 1024): (14691539678,
-                                 "d285ac6b36ad61e52db4c46962ddea1ee97ebb3f000c665c0fc2dbd841f6e989"),
+    ("fork_join", 32768, 1024): (14848771532,
+                                 "67a44e104f16e099dea36c34822eb937c80d0b2db262ae6747e32740fd85dfa9"),
     # lookahead: the bulk of one step (its pool launch and tail summed)
-    ("fork_join_lookahead", 32768, 1024): (13416949907,
-                                           "1aa0c32079a02e7b25a04f42134cbf438851b7525eb701bd9fb9940eede78702"),
+    ("fork_join_lookahead", 32768, 1024): (13497496160,
+                                           "c5da64ba48c0538978c5067563bc1ffbc660329d5c04fcad35ca9ff0a5352dae"),
 }
 # the device code the counters describe: the tile bodies, the DAG decode, the
 # fork-join kernels (unit runners up to the naive variant) of kernels.hip,

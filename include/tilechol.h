@@ -292,8 +292,8 @@ int64_t chol_refine_workspace_size(int64_t n, int64_t T, int64_t nrhs);
  *           slowest column (PCG).
  *   eta     host array of nrhs, or NULL: the final backward errors.
  * The call synchronises `stream` once per iteration (the stopping test).
- * Returns CHOL_OK, CHOL_NOT_CONVERGED (X holds the last iterate),
- * CHOL_ETIMEOUT (a dependency wait of a solve sweep exceeded
+ * Returns CHOL_OK, CHOL_NOT_CONVERGED (X holds the last iterate; the eta of a
+ * column that is not finite is NaN), CHOL_ETIMEOUT (a dependency wait of a solve sweep exceeded
  * chol_set_wait_limit; X unspecified) or a negative error code. */
 int chol_solve_refine(const double* A, int64_t lda, const double* L, int64_t ldl, int64_t n, int64_t T,
                       const double* B, int64_t ldb, double* X, int64_t ldx, int64_t nrhs, int method,
@@ -355,7 +355,8 @@ int chol_factor_solve_batched(double* const* A, double* const* B, const int64_t*
  *           arrays (or NULL) of the corrections applied and the final
  *           backward error per matrix, filled only when info != NULL.
  * Returns CHOL_OK, CHOL_NOT_SPD, CHOL_ETIMEOUT, CHOL_NOT_CONVERGED (a
- * matrix ended above tol), or a negative error code. */
+ * matrix ended above tol, or with a NaN eta as its solution is not finite),
+ * or a negative error code. */
 int64_t chol_factor_solve_batched_mixed_workspace_size(int64_t batch, const int64_t* n, const int64_t* T,
                                                        const int* prec);
 int chol_factor_solve_batched_mixed(const double* const* A, double* const* L, const double* const* B,
@@ -432,7 +433,7 @@ int chol_server_submit_solve(chol_server* server, int64_t factor, const double* 
  * n x nrhs, or NULL) receives the solution, *eta the worst column's backward
  * error, *latency_s the time from submission to the result being in host
  * memory.  Returns CHOL_OK (eta <= tol), CHOL_NOT_CONVERGED (done, eta >
- * tol), CHOL_NOT_SPD (*info as for chol_factor), CHOL_ESTALLED (a dependency
+ * tol, or NaN as the solution is not finite), CHOL_NOT_SPD (*info as for chol_factor), CHOL_ESTALLED (a dependency
  * wait exceeded chol_set_wait_limit, in the request's first run and again
  * in the one restart it is given, and X is unspecified: *info = 1 + the
  * ticket, within its tick's launch, of the factorization unit that waited,
